@@ -12,8 +12,9 @@
 // already in flight.  Each lane then tests one staged entry against the
 // bounding rectangle of each group's still-active pixels (pixel box, then an
 // exact conservative ellipse-rectangle test), the ballots give every group its
-// own stream of entries that can reach it, and each group walks its stream in
-// list order reading records with broadcast LDS loads.  Culled entries never
+// own stream of entries that can reach it (LDS offsets, written by the lanes
+// that tested them), and each group walks its stream in list order reading
+// records with broadcast LDS loads.  Culled entries never
 // reach alpha_min at those pixels, so culling never changes a result.  Groups
 // whose pixels have all stopped drop the rest of their stream, and a wave ends
 // when all its groups have.
@@ -177,10 +178,6 @@ __device__ __forceinline__ uint32_t rows_max_u32(uint32_t x) {
   return h.a > h.b ? h.a : h.b;
 }
 
-struct Sum9 {
-  float v;   // one of the first eight totals (see row_sum9)
-  float v8;  // total of the ninth value
-};
 __device__ __forceinline__ bool box_meets(int2 b, int32_t x0, int32_t x1, int32_t y0, int32_t y1) {
   // pixel box (lo | hi << 16) against the pixel rectangle [x0, x1] x [y0, y1]
   return (int32_t)((uint32_t)b.x >> 16) >= x0 && (b.x & 0xffff) <= x1 && (int32_t)((uint32_t)b.y >> 16) >= y0 &&
@@ -226,6 +223,92 @@ __device__ __forceinline__ Rect group_rect(uint32_t bits, int32_t gx0, int32_t g
   r.x0 = gx0 + (int32_t)__builtin_ctz(cols);
   r.x1 = gx0 + (31 - (int32_t)__builtin_clz(cols));
   return r;
+}
+
+// One staged entry against the pixel centres of a group's rectangle: what
+// ellipse_meets decides, for the many tests of a chunk.  `ox`, `oy`: the centre
+// of the wave's first pixel minus the entry's mean; x0..y1: the rectangle,
+// from that pixel.  A convex quadratic with its minimum outside a rectangle
+// takes its least value there on one of the (at most two) edges that face the
+// minimum, so two edges are tried instead of four: the one at the nearest x
+// and the one at the nearest y (where the minimum lies between the edges, the
+// nearest value is 0 and the point tried is one of the rectangle, so the
+// result is never below the true minimum).  Same margin as ellipse_meets,
+// far above the rounding of the approximate reciprocals.
+struct EntryTest {
+  float ox, oy, A, B, C, hiA, hiC, lim;
+};
+__device__ __forceinline__ EntryTest entry_test(float4 r0, float4 r1, int32_t sx0, int32_t sy0,
+                                                float log2_alpha_min) {
+  EntryTest t;
+  t.ox = ((float)sx0 + 0.5f - r0.x) - r0.z;
+  t.oy = ((float)sy0 + 0.5f - r0.y) - r0.w;
+  t.A = r1.x;
+  t.B = r1.y;
+  t.C = r1.z;
+  t.hiA = -0.5f * r1.y * __builtin_amdgcn_rcpf(r1.x);
+  t.hiC = -0.5f * r1.y * __builtin_amdgcn_rcpf(r1.z);
+  const float budget = r1.w - log2_alpha_min;
+  t.lim = budget + 1e-3f * (1.f + fabsf(budget));
+  return t;
+}
+__device__ __forceinline__ bool group_meets(const EntryTest& t, float x0, float x1, float y0, float y1) {
+  const float lx = t.ox + x0, hx = t.ox + x1, ly = t.oy + y0, hy = t.oy + y1;
+  const float nx = __builtin_amdgcn_fmed3f(0.f, lx, hx), ny = __builtin_amdgcn_fmed3f(0.f, ly, hy);
+  const float yx = __builtin_amdgcn_fmed3f(t.hiC * nx, ly, hy), xy = __builtin_amdgcn_fmed3f(t.hiA * ny, lx, hx);
+  const float qx = nx * (t.A * nx + t.B * yx) + t.C * yx * yx;
+  const float qy = xy * (t.A * xy + t.B * ny) + t.C * ny * ny;
+  return fminf(qx, qy) <= t.lim;
+}
+
+// Streams of a wave's four groups for one chunk of 64 staged entries: the LDS
+// byte offsets (16 per entry) of the entries that can reach the group, in list
+// order, with their counts.  Walking a list of offsets costs a 16-bit LDS read
+// per entry; walking the ballot masks instead costs ten vector instructions
+// per entry (two-word bit scans and clears per lane).
+constexpr int kGroups = 4;
+struct Streams {
+  int n[kGroups];
+  uint64_t any;  // entries in some stream
+};
+__device__ __forceinline__ Streams make_streams(uint16_t (*stream)[kWave], int2 box, float4 r0, float4 r1, bool in,
+                                                uint64_t active, int groups, int32_t sx0, int32_t sy0, int k, int lane,
+                                                float log2_alpha_min) {
+  Streams st;
+  st.any = 0;
+  const EntryTest t = entry_test(r0, r1, sx0, sy0, log2_alpha_min);
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    const uint32_t bits = g < groups ? (uint32_t)(active >> (16 * g)) & 0xffffu : 0u;
+    st.n[g] = 0;
+    if (bits != 0u) {
+      const Rect rg = group_rect(bits, sx0 + (g & 1) * 4, sy0 + (g >> 1) * 4);
+      const bool rel = in && box_meets(box, rg.x0, rg.x1, rg.y0, rg.y1) &&
+                       group_meets(t, (float)(rg.x0 - sx0), (float)(rg.x1 - sx0), (float)(rg.y0 - sy0),
+                                   (float)(rg.y1 - sy0));
+      const uint64_t m = __builtin_amdgcn_ballot_w64(rel);
+      if (rel) stream[g][__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+          (uint16_t)(k * 16);
+      st.n[g] = (int)__popcll(m);
+      st.any |= m;
+    }
+  }
+  // the lanes of this wave read what other lanes of it have written
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return st;
+}
+// The same value, which the compiler does not know to be the same: what is
+// computed from it is computed where it is used instead of being held in
+// registers over the loops in between (registers set how many waves a SIMD
+// holds in these kernels).
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+template <typename T>
+__device__ __forceinline__ T lds_at(const T* base, uint32_t bytes) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
 }
 
 // Work item of a render workgroup.  With a tile order (longest lists first),
@@ -334,7 +417,8 @@ inline int32_t split_tiles(const uint32_t* order, int32_t tiles_total) {
 
 constexpr int kBatch = kBlock;  // list entries staged per workgroup round
 constexpr int kFwdUnroll = 2;   // entries of a group's stream per forward iteration
-constexpr int kBwdUnroll = 1;   // entries of a group's stream per backward iteration
+static_assert(kFwdUnroll == 2, "an iteration's two 16-bit offsets come from one 32-bit read");
+constexpr uint32_t kNoOffset = 0xffffffffu, kNoRecord = 0xffffffffu;
 
 // Work per tile spans four orders of magnitude and a wave's list is walked in
 // order, so the longest lists set the kernel's length.  Waves of long lists
@@ -368,6 +452,9 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   // workgroup with LDS atomics, flushed with one global atomic per entry
   __shared__ float s_acc_w[ACC ? kBatch : 1];
   __shared__ uint32_t s_acc_m[ACC ? kBatch : 1];
+  __shared__ uint16_t s_stream[kBlock / kWave][kGroups][kWave];
+  // an offset read past a stream's end is unused, but it is read: keep it in range
+  for (int q = threadIdx.x; q < kBlock / kWave * kGroups * kWave; q += kBlock) (&s_stream[0][0][0])[q] = 0;
   const WorkItem wi = work_item(order, ranges, nsplit, vs.tiles_total, true);
   if (wi.skip) return;
   const int32_t tile = wi.tile;
@@ -384,17 +471,19 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   const int grp = lane >> 4;
   const bool rp = wi.quarter >= 0 && wi.rowpar;  // split work item: rows are consecutive entries
   const LanePixel lp = lane_pixel(tx, ty, wi.quarter, wv, lane, rp);
-  const int32_t sx0 = lp.sx0, sy0 = lp.sy0, px = lp.px, py = lp.py;
-  const bool inside = lp.on && px < cam.width && py < cam.height;
-  const float pxc = (float)px + 0.5f, pyc = (float)py + 0.5f;
+  const int32_t sx0 = lp.sx0, sy0 = lp.sy0;
+  const bool inside = lp.on && lp.px < cam.width && lp.py < cam.height;
+  const float pxc = (float)lp.px + 0.5f, pyc = (float)lp.py + 0.5f;
   const uint32_t start = uload(ranges + 2 * tile), end = uload(ranges + 2 * tile + 1);
   const int64_t vbase = (int64_t)v * n;
   const int64_t nrec = (int64_t)vs.count * n;
   set_wave_priority(end - start);
   float T = 1.f, c0 = 0.f, c1 = 0.f, c2 = 0.f, wbest = 0.f, dblend = 0.f;
-  int32_t best = -1;
+  uint32_t best = kNoRecord;  // record index
   uint32_t lastpos = 0, cnt = 0;
-  uint32_t bpos = 0xffffffffu;  // list position of `best` (split work items)
+  // split work items: list position of `best`; others: LDS offset of the last
+  // entry of this round that the pixel has composited
+  uint32_t at = kNoOffset;
   bool done = !inside;
   // Staging pipeline: while round R is processed, the records of round R + 1
   // and the list indices of round R + 2 are already in flight.
@@ -420,41 +509,27 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
     }
     const uint32_t count = (end - base) < (uint32_t)kBatch ? (end - base) : (uint32_t)kBatch;
     bool wave_done = __all(done);
+    if (!rp) at = kNoOffset;
+#pragma unroll 1
     for (int c = 0; c < kBatch / kWave && !wave_done; ++c) {
       // staged entry k against each group's still-compositing pixels
       const int k = c * kWave + lane;
       const bool kin = (uint32_t)k < count;
       const int2 bx = s_box[k];
       const float4 q0 = s_r0[k], q1 = s_r1[k];
-      const uint64_t am = __ballot(!done);
-      uint64_t gmask[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const uint32_t bits = (rp && g > 0) ? 0u : (uint32_t)(am >> (16 * g)) & 0xffffu;
-        bool rel = false;
-        if (bits != 0u) {
-          const Rect rg = group_rect(bits, sx0 + (g & 1) * 4, sy0 + (g >> 1) * 4);
-          rel = kin && box_meets(bx, rg.x0, rg.x1, rg.y0, rg.y1) &&
-                ellipse_meets(q0, q1, rg.x0, rg.x1, rg.y0, rg.y1, op.log2_alpha_min);
-        }
-        gmask[g] = __ballot(rel);
-      }
-      uint64_t mine = rp ? gmask[0] : grp == 0 ? gmask[0] : grp == 1 ? gmask[1] : grp == 2 ? gmask[2] : gmask[3];
+      const uint64_t am = __builtin_amdgcn_ballot_w64(!done);
+      const Streams st = make_streams(s_stream[wv], bx, q0, q1, kin, am, rp ? 1 : kGroups, sx0, sy0, k, lane,
+                                      op.log2_alpha_min);
       // Split work item: row r takes the r-th of the next four entries of the
       // group's stream.  The transmittance in front of each is T times the
       // product of (1 - alpha) over the rows before it; an entry is composited
       // unless its own or an earlier row's entry reaches the stop.  Each row
       // keeps partial colour, depth, count and argmax, merged at the end.
-      uint64_t rmine = rp ? uniform_u64(mine) : 0ull;  // the same in every lane: keep it scalar
-      if (rp) mine = 0;
-      while (rmine != 0) {
-        // row r's entry: the lowest set bit of the mask with r lower bits cleared
-        const uint64_t m1 = rmine & (rmine - 1), m2 = m1 & (m1 - 1), m3 = m2 & (m2 - 1);
-        const uint64_t mr = grp < 2 ? (grp == 0 ? rmine : m1) : (grp == 2 ? m2 : m3);
-        rmine = m3 & (m3 - 1);
-        const bool hr = mr != 0;
-        const int kr = c * kWave + (hr ? (int)__builtin_ctzll(mr) : 0);
-        const float4 r0 = s_r0[kr], r1 = s_r1[kr], q2 = s_r2[kr];
+      int left = rp ? st.n[0] : 0;
+      for (const uint16_t* sp = &s_stream[wv][0][grp]; left > 0; left -= kGroups, sp += kGroups) {
+        const bool hr = grp < left;
+        const uint32_t off = hr ? *sp : 0u;
+        const float4 r0 = lds_at(s_r0, off), r1 = lds_at(s_r1, off), q2 = lds_at(s_r2, off);
         const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
         const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
         const float al = fminf(op.alpha_max, __builtin_amdgcn_exp2f(ee));
@@ -462,15 +537,16 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
         const float om = pass ? 1.f - al : 1.f;
         const RowScan tf = rows_scan_mul(om, grp);
         const bool stop = pass && T * tf.incl < op.t_min;
-        const uint64_t sb = __ballot(stop);
+        const uint64_t sb = __builtin_amdgcn_ballot_w64(stop);
         bool inc = pass;
         float Tn = T * tf.total;
         if (sb != 0ull) {
           // rare: some pixel stops at one of these entries; later rows of its
           // column are dropped and its transmittance is the one in front of
           // the stopping entry
-          const uint64_t col = 0x0001000100010001ull << (lane & 15);
-          const bool earlier = (sb & col & ((1ull << (16 * grp)) - 1ull)) != 0;
+          const int l = fresh(lane);
+          const uint64_t col = 0x0001000100010001ull << (l & 15);
+          const bool earlier = (sb & col & ((1ull << (l & 48)) - 1ull)) != 0;
           inc = pass && !stop && !earlier;
           Tn = T * rows_scan_mul(inc ? om : 1.f, grp).total;
           done = done || (sb & col) != 0;
@@ -479,48 +555,55 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
         c0 += wgt * q2.x;
         c1 += wgt * q2.y;
         c2 += wgt * q2.z;
-        if (DEPTH == GS_DEPTH_BLEND) dblend += wgt * s_z[kr];
-        const uint32_t pos = base + (uint32_t)kr - start;
+        if (DEPTH == GS_DEPTH_BLEND) dblend += wgt * lds_at(s_z, off >> 2);
+        const uint32_t pos = base + (off >> 4) - start;
         const bool better = wgt > wbest;  // a row's entries arrive in order: the nearer wins ties
         wbest = better ? wgt : wbest;
-        best = better ? (int32_t)((int64_t)__float_as_uint(q2.w) - vbase) : best;
-        bpos = better ? pos : bpos;
+        best = better ? __float_as_uint(q2.w) : best;
+        at = better ? pos : at;
         lastpos = inc ? pos + 1 : lastpos;
         cnt += inc ? 1u : 0u;
         if (ACC && inc) {
-          atomicAdd(&s_acc_w[kr], wgt);
-          atomicMax(&s_acc_m[kr], __float_as_uint(wgt));
+          atomicAdd(&s_acc_w[off >> 4], wgt);
+          atomicMax(&s_acc_m[off >> 4], __float_as_uint(wgt));
         }
         T = Tn;
         if (sb != 0ull) {
-          const uint64_t dm = __ballot(done);
-          if ((dm & 0xffffull) == 0xffffull) rmine = 0;
+          const uint64_t dm = __builtin_amdgcn_ballot_w64(done);
+          if ((dm & 0xffffull) == 0xffffull) left = 0;
           if (dm == ~0ull) {
             wave_done = true;
             break;
           }
         }
       }
+      if (rp) continue;
       // kFwdUnroll entries of the group's stream per iteration: their records
       // are read and their alphas evaluated side by side, then they are
       // composited in order (each sees the previous one's transmittance and
       // stop), so the result is that of one-by-one compositing with a fraction
-      // of the loop latency.
-      while (__any(mine != 0)) {
-        int kk[kFwdUnroll];
+      // of the loop latency.  The offsets of the next iteration are read ahead.
+      int mine = grp == 0 ? st.n[0] : grp == 1 ? st.n[1] : grp == 2 ? st.n[2] : st.n[3];
+      const int n01 = st.n[0] > st.n[1] ? st.n[0] : st.n[1], n23 = st.n[2] > st.n[3] ? st.n[2] : st.n[3];
+      const int longest = n01 > n23 ? n01 : n23;
+      const uint32_t* sp = reinterpret_cast<const uint32_t*>(&s_stream[wv][grp][0]);
+      uint32_t pair = *sp;
+      for (int i = 0; i < longest; i += kFwdUnroll) {
+        uint32_t off[kFwdUnroll];
         bool has[kFwdUnroll];
 #pragma unroll
         for (int u = 0; u < kFwdUnroll; ++u) {
-          has[u] = mine != 0;
-          kk[u] = c * kWave + (has[u] ? (int)__builtin_ctzll(mine) : 0);
-          mine &= mine - 1;
+          has[u] = i + u < mine;
+          off[u] = (pair >> (16 * u)) & 0xffffu;
         }
+        sp += i + kFwdUnroll < kWave ? 1 : 0;
+        pair = *sp;
         float4 q2[kFwdUnroll];
         float al[kFwdUnroll], ee[kFwdUnroll];
 #pragma unroll
         for (int u = 0; u < kFwdUnroll; ++u) {
-          const float4 r0 = s_r0[kk[u]], r1 = s_r1[kk[u]];
-          q2[u] = s_r2[kk[u]];
+          const float4 r0 = lds_at(s_r0, off[u]), r1 = lds_at(s_r1, off[u]);
+          q2[u] = lds_at(s_r2, off[u]);
           const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
           ee[u] = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
           al[u] = fminf(op.alpha_max, __builtin_amdgcn_exp2f(ee[u]));
@@ -540,22 +623,22 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
           c0 += wgt * q2[u].x;
           c1 += wgt * q2[u].y;
           c2 += wgt * q2[u].z;
-          if (DEPTH == GS_DEPTH_BLEND) dblend += wgt * s_z[kk[u]];
+          if (DEPTH == GS_DEPTH_BLEND) dblend += wgt * lds_at(s_z, off[u] >> 2);
           const bool better = wgt > wbest;  // strict: the nearer entry wins ties
           wbest = better ? wgt : wbest;
-          best = better ? (int32_t)((int64_t)__float_as_uint(q2[u].w) - vbase) : best;
-          lastpos = inc ? base + (uint32_t)kk[u] - start + 1 : lastpos;
+          best = better ? __float_as_uint(q2[u].w) : best;
+          at = inc ? off[u] : at;
           cnt += inc ? 1u : 0u;
           if (ACC && inc) {
             // each including lane adds its weight to the entry's LDS slot (no
             // reply awaited, so nothing on this wave's dependency chain);
             // weights are >= 0, so the max runs on bit patterns
-            atomicAdd(&s_acc_w[kk[u]], wgt);
-            atomicMax(&s_acc_m[kk[u]], __float_as_uint(wgt));
+            atomicAdd(&s_acc_w[off[u] >> 4], wgt);
+            atomicMax(&s_acc_m[off[u] >> 4], __float_as_uint(wgt));
           }
         }
         // a group whose pixels have all stopped drops the rest of its stream
-        const uint64_t dm = __ballot(done);
+        const uint64_t dm = __builtin_amdgcn_ballot_w64(done);
         if (((dm >> (16 * grp)) & 0xffffull) == 0xffffull) mine = 0;
         if (dm == ~0ull) {
           wave_done = true;
@@ -563,6 +646,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
         }
       }
     }
+    if (!rp && at != kNoOffset) lastpos = base - start + (at >> 4) + 1;
     if (ACC) {
       __syncthreads();
       if ((uint32_t)threadIdx.x < count && s_acc_m[threadIdx.x] != 0u) {
@@ -585,18 +669,21 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
 #pragma unroll
     for (int step = 0; step < 2; ++step) {
       const RowsTwo w = step == 0 ? rows_pair(__float_as_uint(wbest)) : rows_halves(__float_as_uint(wbest));
-      const RowsTwo b = step == 0 ? rows_pair((uint32_t)best) : rows_halves((uint32_t)best);
-      const RowsTwo q = step == 0 ? rows_pair(bpos) : rows_halves(bpos);
+      const RowsTwo b = step == 0 ? rows_pair(best) : rows_halves(best);
+      const RowsTwo q = step == 0 ? rows_pair(at) : rows_halves(at);
       const float wa = __uint_as_float(w.a), wb = __uint_as_float(w.b);
       const bool take_b = wb > wa || (wb == wa && q.b < q.a);
       wbest = take_b ? wb : wa;
-      best = (int32_t)(take_b ? b.b : b.a);
-      bpos = take_b ? q.b : q.a;
+      best = take_b ? b.b : b.a;
+      at = take_b ? q.b : q.a;
     }
     if (grp != 0) return;  // row 0 writes the pixel
   }
-  if (!inside) return;
-  if (ACC && o.area && best >= 0) atomicAdd(o.area + (per_view ? vbase + best : (int64_t)best), 1u);
+  const LanePixel le = lane_pixel(tx, ty, wi.quarter, wv, fresh(lane), rp);
+  const int32_t px = le.px, py = le.py;
+  if (!le.on || px >= cam.width || py >= cam.height) return;
+  const int32_t gbest = best == kNoRecord ? -1 : (int32_t)((int64_t)best - vbase);
+  if (ACC && o.area && gbest >= 0) atomicAdd(o.area + (per_view ? vbase + gbest : (int64_t)gbest), 1u);
   if (!OUT) return;
   const int64_t P = vs.pixels_total;
   const int64_t gp = cam.pixel_base + (int64_t)py * cam.width + px;
@@ -605,20 +692,20 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   o.color[2 * P + gp] = c2 + T * op.bg[2];
   o.t_final[gp] = T;
   o.last[gp] = lastpos;
-  o.imax[gp] = best;
+  o.imax[gp] = gbest;
   if (o.n_contrib) o.n_contrib[gp] = cnt;
   float dep = 0.f;
   uint8_t h = 0;
-  if (best >= 0 && (o.depth || o.hit)) {
+  if (gbest >= 0 && (o.depth || o.hit)) {
     RayCam rc;
     for (int k = 0; k < 9; ++k) rc.R[k] = cam.R[k];
     for (int k = 0; k < 3; ++k) rc.t[k] = cam.t[k];
     rc.fx = cam.fx; rc.fy = cam.fy; rc.cx = cam.cx; rc.cy = cam.cy;
-    const MidDepth md = mid_depth(rc, means, scales, quats, n, best, pxc, pyc);
+    const MidDepth md = mid_depth(rc, means, scales, quats, n, gbest, pxc, pyc);
     const float dm = md.depth;
     h = (uint8_t)md.hit;
     if (DEPTH == GS_DEPTH_MID) dep = dm;
-    else if (DEPTH == GS_DEPTH_CENTER) dep = rec[(vbase + best) * kRecFloats + 12];
+    else if (DEPTH == GS_DEPTH_CENTER) dep = rec[(vbase + gbest) * kRecFloats + 12];
     else dep = dblend;
   }
   if (o.depth) o.depth[gp] = dep;
@@ -628,21 +715,14 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
 // ---------------------------------------------------------------------------
 // backward
 // ---------------------------------------------------------------------------
-// Same staging as the forward, walking rounds and entries back to front from
-// the largest `last` of the workgroup.  Per pixel: restore the transmittance
-// in front of the Gaussian (T /= 1 - alpha), form dL/dalpha from the colour
-// composited behind it, and add the Gaussian's own weighted colour to that
-// suffix.  Entries of inactive Gaussians update the per-pixel state but emit
-// no gradient.  The nine partials of an entry are summed over the wave with
-// DPP and added by one lane to the record's 2D gradient.
-// One list entry for the backward: as Staged, plus the rest of the record
-// (z and the conic) and the active flag in bit 31 of the index.  A corrupt
-// index (outside this view's records) is replaced by an inactive entry with an
-// empty box.
+// One list entry for the backward: the first 48 bytes of its record, with the
+// opacity negated for an inactive entry (a drawn record's opacity is positive),
+// so the walk needs no separate flag.  A corrupt index (outside this view's
+// records) is replaced by an inactive entry with an empty box.
 struct StagedB {
-  uint32_t tag;
+  uint32_t idx;
   int2 box;
-  float4 r0, r1, r2, r3;
+  float4 r0, r1, r2;
 };
 template <bool MASKED>
 __device__ __forceinline__ StagedB fetch_entry_bwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
@@ -651,69 +731,97 @@ __device__ __forceinline__ StagedB fetch_entry_bwd(const float* __restrict__ rec
   StagedB e;
   const bool valid = in_list && (int64_t)r < nrec && (int64_t)r >= vbase;
   r = valid ? r : (uint32_t)vbase;
-  const uint32_t act = (valid && (!MASKED || active[(int64_t)r - vbase] != 0)) ? 1u : 0u;
-  e.tag = r | (act << 31);
+  const bool act = valid && (!MASKED || active[(int64_t)r - vbase] != 0);
+  e.idx = r;
   e.box = valid ? *reinterpret_cast<const int2*>(bin + 4 * (int64_t)r) : make_int2(0xffff, 0xffff);
   const float4* R4 = reinterpret_cast<const float4*>(rec + (int64_t)r * kRecFloats);
   e.r0 = R4[0];
   e.r1 = R4[1];
   e.r2 = R4[2];
-  e.r3 = R4[3];
+  e.r2.w = act ? fabsf(e.r2.w) : -fabsf(e.r2.w);
   return e;
 }
 
-// Sum of nine per-lane partials over each 16-lane row by a butterfly
-// reduce-scatter: three exchange steps (lane xor 1 and xor 2 by quad
-// permutes, xor 8 by a row rotate) halve the values each lane carries, then a
-// row rotate by 4 (lane L reads lane L - 4 mod 16, which is L xor 4 where bit
-// 2 of L is set) adds the last pair.  Afterwards lane L of a row with bit 2
-// set holds the row total of value 4 (L & 1) + 2 ((L >> 1) & 1) +
-// ((L >> 3) & 1), and every lane holds the row total of the ninth value (a
-// plain chain).
-__device__ __forceinline__ Sum9 row_sum9(const float (&p)[9], int lane) {
-  constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kRor8 = 0x128, kRor4 = 0x124;
-  const bool o1 = (lane & 1) != 0, o2 = (lane & 2) != 0, o8 = (lane & 8) != 0;
-  float a[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float keep = o1 ? p[4 + j] : p[j], send = o1 ? p[j] : p[4 + j];
-    a[j] = keep + dpp_take<kXor1>(send);
-  }
-  float c[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const float keep = o2 ? a[2 + j] : a[j], send = o2 ? a[j] : a[2 + j];
-    c[j] = keep + dpp_take<kXor2>(send);
-  }
-  float d = (o8 ? c[1] : c[0]) + dpp_take<kRor8>(o8 ? c[0] : c[1]);
-  d += dpp_take<kRor4>(d);  // lanes with bit 2 set: partner is lane ^ 4
-  float e = p[8] + dpp_take<kXor1>(p[8]);
-  e += dpp_take<kXor2>(e);
-  e += dpp_take<kRor4>(e);
-  e += dpp_take<kRor8>(e);
-  Sum9 r;
-  r.v = d;
-  r.v8 = e;
-  return r;
+// Sum of nine per-lane partials over each 16-lane row.  Each step adds the
+// other half of the lanes and keeps one value in either half: lanes 8 apart
+// (a row rotate; values 2 j and 2 j + 1 share a register), then the two quads
+// of a half row (its mirror), then the lanes of a quad.  The halves are chosen
+// by the bank mask of the add itself (lanes of a disabled bank keep the
+// register's value), so a pair of values costs two instructions and no
+// selects, which the compiler cannot express: hence the assembly.  A DPP read
+// needs two instructions after the write of its register; the order below
+// keeps that distance.  Returned: in lane L of a row the total of value
+// sum_slot(L), where that is not negative.
+__device__ __forceinline__ int sum_slot(int lane) {
+  const int q = (lane >> 2) & 3, t = 2 * (q & 1) + (q >> 1);  // quads hold values 0, 2, 1, 3 and 4, 6, 5, 7
+  const int r = lane & 3;
+  return r == 0 ? t : r == 1 ? 4 + t : (lane & 15) == 2 ? 8 : -1;
+}
+__device__ __forceinline__ float row_sum9(const float (&p)[9], int lane) {
+  float a, b, c, d, e, f, h;
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %7, %7 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %11, %11 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %3, %13, %13 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %12, %12 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %3, %14, %14 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %6, %15, %15 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %5, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %6, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %5, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d), "=&v"(e), "=&v"(f), "=&v"(h)
+      : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]), "v"(p[8]));
+  const int r = lane & 3;
+  return r == 0 ? e : r == 1 ? f : h;
 }
 
-// One group's summed partials of one entry leave the row: nine lanes add them
-// to the record's 2D gradient with float atomics, or (deterministic
-// reduction) store them in the entry's slot for this group (list position j,
-// group g16 of the tile's sixteen 4x4 groups) and mark the slot in the
-// entry's mask.  A slot is written at most once: each group walks an entry at
-// most once.
+// The nine sums of an entry over pixels, with e = dL/dalpha alpha (0 where
+// alpha is clamped or the entry is not composited) and w the weight:
+//   0, 1: sum e dx, e dy   2, 3, 4: sum e dx dx, e dx dy, e dy dy
+//   5: sum e               6, 7, 8: sum w dL/dcolour
+// What the 2D gradient adds to them is constant per record (conic, opacity),
+// so it is applied once to the sums (g2d_component) instead of per pixel.
+//
+// Component c of the record's 2D gradient from its sums: dL/du = a S0 + b S1,
+// dL/dv = b S0 + c S1 with the conic (a, b, c) = (2 A, B, 2 C) / log2(e) of the
+// staged (A, B, C); dL/d(conic) = (-S2 / 2, -S3, -S4 / 2); dL/d(opacity) =
+// S5 / opacity; the colour sums as they are.
+// x = Sc, and y the other of S0 and S1 for c < 2.
+__device__ __forceinline__ float g2d_component(int c, float x, float y, float A, float B, float C, float opacity) {
+  constexpr float kLn2 = 0.6931471805599453f;
+  const float pair = kLn2 * (2.f * (c == 0 ? A : C) * x + B * y);
+  const float scale = c == 5 ? __builtin_amdgcn_rcpf(opacity) : c > 5 ? 1.f : c == 3 ? -1.f : -0.5f;
+  return c < 2 ? pair : scale * x;
+}
+
+// One group's sums of one entry leave the row from nine of its lanes: into the
+// entry's accumulators in LDS, which the workgroup adds to the record's 2D
+// gradient once per round, or (deterministic reduction) into the entry's slot
+// for this group (list position j, group g16 of the tile's sixteen 4x4
+// groups), marked in the entry's mask.  A slot is written at most once: each
+// group walks an entry at most once.
 template <bool DET>
-__device__ __forceinline__ void emit_partial(float* __restrict__ g2d, float* __restrict__ part,
-                                             uint32_t* __restrict__ pmask, uint32_t tag, uint32_t j, int g16,
-                                             int slot, uint64_t cm, int grp, const Sum9& r) {
+__device__ __forceinline__ void emit_partial(float* s_acc, float* __restrict__ part, uint32_t* __restrict__ pmask,
+                                             uint32_t k, uint32_t base, int g16, int slot, uint64_t cm, int grp,
+                                             float val) {
   if (slot < 0 || ((cm >> (16 * grp)) & 0xffffull) == 0) return;
-  const float val = slot == 8 ? r.v8 : r.v;
   if (DET) {
+    const uint32_t j = base + k;
     part[((int64_t)j * 16 + g16) * kG2d + slot] = val;
     if (slot == 8) atomicOr(pmask + j, 1u << g16);
   } else {
-    atomicAdd(g2d + (int64_t)(tag & 0x7fffffffu) * kG2d + slot, val);
+    atomicAdd(s_acc + (uint32_t)__umul24(k, (uint32_t)kG2d) + slot, val);
   }
 }
 
@@ -721,10 +829,17 @@ __device__ __forceinline__ void emit_partial(float* __restrict__ g2d, float* __r
 // entries back to front from the largest `last` of the workgroup.  Per pixel:
 // restore the transmittance in front of the Gaussian (T /= 1 - alpha), form
 // dL/dalpha from the colour composited behind it, and add the Gaussian's own
-// weighted colour to that suffix.  Entries of inactive Gaussians update the
-// per-pixel state but emit no gradient.  The nine partials of a group's entry
-// are summed over its 16 lanes in registers and added by nine of its lanes
-// to the record's 2D gradient.
+// weighted colour to that suffix.  Only the products of the colours with
+// dL/dcolour enter dL/dalpha, so the suffix is that one scalar.  Entries of
+// inactive Gaussians update the per-pixel state but emit no gradient.  The
+// nine sums of a group's entry are formed over its 16 lanes in registers and
+// added by nine of its lanes to the entry's accumulators in LDS; after each
+// round the workgroup adds them, converted, to the records' 2D gradients.
+// One global atomic per (entry, workgroup) and component instead of one per
+// (entry, group): float atomics are carried out at the memory side (at most
+// ~17 G requests/s), which bounded the kernel where most entries are active
+// (1M Gaussians, 16 views, 17.3M pixels, all active: 169M -> 31M requests,
+// with the streams below and the scalar suffix 9.76 -> 6.42 ms).
 template <bool MASKED, bool DET>
 __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
                                                        const uint32_t* __restrict__ vals,
@@ -736,9 +851,18 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
                                                        const uint8_t* __restrict__ active, float* __restrict__ g2d,
                                                        float* __restrict__ part, uint32_t* __restrict__ pmask,
                                                        KOpts op, ViewSet vs) {
-  __shared__ float4 s_r0[kBatch], s_r1[kBatch], s_r2[kBatch], s_r3[kBatch];
+  __shared__ float4 s_r0[kBatch], s_r1[kBatch], s_r2[kBatch];
   __shared__ int2 s_box[kBatch];
-  __shared__ uint32_t s_idx[kBatch];  // record index | active << 31
+  __shared__ uint32_t s_idx[DET ? 1 : kBatch];
+  // the staged entries' sums over the workgroup; all zero at the start of a round
+  __shared__ float s_acc[DET ? 1 : kBatch * kG2d];
+  constexpr int kChunks = kBatch / kWave;
+  __shared__ uint64_t s_walk[kChunks][kBlock / kWave];  // entries of a chunk that a wave may have walked
+  __shared__ uint8_t s_list[kChunks][kWave];
+  __shared__ uint16_t s_stream[kBlock / kWave][kGroups][kWave];
+  for (int q = threadIdx.x; q < kBlock / kWave * kGroups * kWave; q += kBlock) (&s_stream[0][0][0])[q] = 0;
+  if (!DET)
+    for (int q = threadIdx.x; q < kBatch * kG2d; q += kBlock) s_acc[q] = 0.f;
   __shared__ uint32_t s_jmax[kBlock / kWave];
   const WorkItem wi = work_item(order, ranges, nsplit, vs.tiles_total, false);
   if (wi.skip) return;
@@ -773,10 +897,8 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
     g2 = dldc[2 * P + gp];
   }
   lst = lst < end - start ? lst : end - start;  // `last` never exceeds the tile's list
-  float s0 = T * op.bg[0], s1 = T * op.bg[1], s2 = T * op.bg[2];
-  // 2D-gradient component this lane adds after row_sum9, or -1
-  const int l16 = lane & 15;
-  const int slot = (l16 & 4) != 0 ? 4 * (l16 & 1) + 2 * ((l16 >> 1) & 1) + ((l16 >> 3) & 1) : (l16 == 0 ? 8 : -1);
+  float S = T * (g0 * op.bg[0] + g1 * op.bg[1] + g2 * op.bg[2]);  // dL/dcolour . colour composited behind
+  const int slot = sum_slot(lane);  // the sum this lane emits after row_sum9, or -1
   const uint32_t wjmax = uniform_u32(wave_max_u32(lst));
   if (lane == 0) s_jmax[wv] = wjmax;
   __syncthreads();
@@ -796,12 +918,14 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   while (top > start) {
     const uint32_t count = top - base;
     __syncthreads();  // the previous round's entries are consumed
-    s_idx[threadIdx.x] = cur.tag;
+    if (!DET) {
+      s_idx[threadIdx.x] = cur.idx;
+      if (threadIdx.x < kChunks * (kBlock / kWave)) (&s_walk[0][0])[threadIdx.x] = 0ull;
+    }
     s_box[threadIdx.x] = cur.box;
     s_r0[threadIdx.x] = cur.r0;
     s_r1[threadIdx.x] = cur.r1;
     s_r2[threadIdx.x] = cur.r2;
-    s_r3[threadIdx.x] = cur.r3;
     __syncthreads();
     {
       // next round [nbase, ntop) and the one after it
@@ -809,154 +933,134 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       const uint32_t nnbase = round_base(nbase);
       nidx = (nbase > start && nnbase + threadIdx.x < nbase) ? vals[nnbase + threadIdx.x] : 0u;
     }
+#pragma unroll 1
     for (int c = kBatch / kWave - 1; c >= 0; --c) {
       const int k = c * kWave + lane;
       // lanes that still have work in this chunk: their last entry lies above its first
-      const uint64_t am = __ballot(lst > base + (uint32_t)(c * kWave) - start);
+      const uint64_t am = __builtin_amdgcn_ballot_w64(lst > base + (uint32_t)(c * kWave) - start);
       if (am == 0) continue;
       const bool kin = (uint32_t)k < count && base + (uint32_t)k < start + wjmax;
       const int2 bx = s_box[k];
       const float4 q0 = s_r0[k], q1 = s_r1[k];
-      uint64_t gmask[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const uint32_t bits = (rp && g > 0) ? 0u : (uint32_t)(am >> (16 * g)) & 0xffffu;
-        bool rel = false;
-        if (bits != 0u) {
-          const Rect rg = group_rect(bits, sx0 + (g & 1) * 4, sy0 + (g >> 1) * 4);
-          rel = kin && box_meets(bx, rg.x0, rg.x1, rg.y0, rg.y1) &&
-                ellipse_meets(q0, q1, rg.x0, rg.x1, rg.y0, rg.y1, op.log2_alpha_min);
-        }
-        gmask[g] = __ballot(rel);
-      }
-      uint64_t mine = rp ? gmask[0] : grp == 0 ? gmask[0] : grp == 1 ? gmask[1] : grp == 2 ? gmask[2] : gmask[3];
+      const Streams st = make_streams(s_stream[wv], bx, q0, q1, kin, am, rp ? 1 : kGroups, sx0, sy0, k, lane,
+                                      op.log2_alpha_min);
+      if (!DET && lane == 0) s_walk[c][wv] = st.any;
+      // round-relative offset from which on the pixel composited nothing
+      const uint32_t lim = lst > base - start ? (lst - (base - start)) * 16u : 0u;
       // Split work item: row r takes the r-th latest of the next four entries
       // of the group's stream.  The transmittance in front of each is the
       // product of 1 / (1 - alpha) over the rows up to it, its suffix colour
       // the sum of the weighted colours of the rows before it; the nine
       // partials of each row's entry are then summed over the row as usual.
-      uint64_t rmine = rp ? uniform_u64(mine) : 0ull;  // the same in every lane: keep it scalar
-      if (rp) mine = 0;
-      while (rmine != 0) {
-        // row r's entry: the highest set bit of the mask with r higher bits cleared
-        auto drop_top = [](uint64_t m) { return m != 0 ? m & ~(1ull << (63 - __builtin_clzll(m))) : 0ull; };
-        const uint64_t m1 = drop_top(rmine), m2 = drop_top(m1), m3 = drop_top(m2);
-        const uint64_t mr = grp < 2 ? (grp == 0 ? rmine : m1) : (grp == 2 ? m2 : m3);
-        rmine = drop_top(m3);
-        const bool hr = mr != 0;
-        const int kr = c * kWave + (hr ? 63 - (int)__builtin_clzll(mr) : 0);
-        const bool val = hr && base + (uint32_t)kr - start < lst;
-        const uint32_t tag = s_idx[kr];
-        const float4 r0 = s_r0[kr], r1 = s_r1[kr], c4 = s_r2[kr], r3 = s_r3[kr];
+      int left = rp ? st.n[0] : 0;
+      for (const uint16_t* sp = &s_stream[wv][0][0] + left - 1 - grp; left > 0; left -= kGroups, sp -= kGroups) {
+        const bool hr = grp < left;
+        const uint32_t off = hr ? *sp : 0u;
+        const bool val = hr && off < lim;
+        const float4 r0 = lds_at(s_r0, off), r1 = lds_at(s_r1, off), c4 = lds_at(s_r2, off);
         const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
         const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
         const float G2 = __builtin_amdgcn_exp2f(ee);
         const bool inc = val && ee >= op.log2_alpha_min;
-        const bool act = inc && (tag >> 31) != 0;
+        const bool act = inc && c4.w > 0.f;
         const float al = fminf(op.alpha_max, G2);
         const float iom = __builtin_amdgcn_rcpf(1.f - al);
         const RowScan tr = rows_scan_mul(inc ? iom : 1.f, grp);
         const float Tr = T * tr.incl;
         const float wgt = inc ? al * Tr : 0.f;
-        const RowScan u0 = rows_scan_add(wgt * c4.x, grp), u1 = rows_scan_add(wgt * c4.y, grp),
-                      u2 = rows_scan_add(wgt * c4.z, grp);
-        const float sr0 = s0 + u0.excl, sr1 = s1 + u1.excl, sr2 = s2 + u2.excl;
-        const float ga = g0 * (Tr * c4.x - sr0 * iom) + g1 * (Tr * c4.y - sr1 * iom) + g2 * (Tr * c4.z - sr2 * iom);
+        const float cg = g0 * c4.x + g1 * c4.y + g2 * c4.z;
+        const RowScan us = rows_scan_add(wgt * cg, grp);
+        const float ga = Tr * cg - (S + us.excl) * iom;
         float pv[9];
         const float wa = act ? wgt : 0.f;
         pv[6] = wa * g0;
         pv[7] = wa * g1;
         pv[8] = wa * g2;
         const float gal = (act && G2 < op.alpha_max) ? ga * al : 0.f;
-        pv[5] = gal != 0.f ? gal * __builtin_amdgcn_rcpf(c4.w) : 0.f;
-        const float gq = -0.5f * gal;
-        pv[2] = gq * dx * dx;
-        pv[3] = 2.f * gq * dx * dy;
-        pv[4] = gq * dy * dy;
-        pv[0] = -2.f * gq * (r3.y * dx + r3.z * dy);
-        pv[1] = -2.f * gq * (r3.z * dx + r3.w * dy);
+        pv[5] = gal;
+        pv[0] = gal * dx;
+        pv[1] = gal * dy;
+        pv[2] = pv[0] * dx;
+        pv[3] = pv[0] * dy;
+        pv[4] = pv[1] * dy;
         T = T * tr.total;
-        s0 += u0.total;
-        s1 += u1.total;
-        s2 += u2.total;
-        const uint64_t cm = __ballot(act);
-        if (cm != 0) {
-          const Sum9 r = row_sum9(pv, lane);
-          emit_partial<DET>(g2d, part, pmask, tag, base + (uint32_t)kr, g16, slot, cm, grp, r);
-        }
+        S += us.total;
+        const uint64_t cm = __builtin_amdgcn_ballot_w64(act);
+        if (cm != 0) emit_partial<DET>(s_acc, part, pmask, off >> 4, base, g16, slot, cm, grp, row_sum9(pv, lane));
       }
-      // kBwdUnroll entries of the group's stream per iteration, latest first:
-      // records and alphas side by side, then the transmittance is restored
-      // through them in reverse order, exactly as one by one.
-      while (__any(mine != 0)) {
-        int kk[kBwdUnroll];
-        bool val[kBwdUnroll];
+      if (rp) continue;
+      // One entry of the group's stream per iteration, latest first; the
+      // transmittance is restored through them in reverse order.
+      const int mine = grp == 0 ? st.n[0] : grp == 1 ? st.n[1] : grp == 2 ? st.n[2] : st.n[3];
+      const int n01 = st.n[0] > st.n[1] ? st.n[0] : st.n[1], n23 = st.n[2] > st.n[3] ? st.n[2] : st.n[3];
+      const int longest = n01 > n23 ? n01 : n23;
+      const uint16_t* const first = &s_stream[wv][grp][0];
+      const uint16_t* sp = first + (mine > 0 ? mine - 1 : 0);
+      uint32_t off = *sp;
+      for (int i = 0; i < longest; ++i) {
+        const uint32_t at = off;
+        const bool val = i < mine && at < lim;
+        sp -= i + 1 < mine ? 1 : 0;
+        off = *sp;
+        const float4 r0 = lds_at(s_r0, at), r1 = lds_at(s_r1, at), c4 = lds_at(s_r2, at);
+        const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
+        const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
+        const float G2 = __builtin_amdgcn_exp2f(ee);
+        // Branch-free per lane: a lane that skips the entry multiplies its
+        // partials by zero and keeps its transmittance; staged records are
+        // finite, so the zero products are zeros.  Transmittance in front of
+        // the entry, its partials, then its colour joins the suffix.
+        const bool inc = val && ee >= op.log2_alpha_min;
+        const bool act = inc && c4.w > 0.f;
+        const float al = fminf(op.alpha_max, G2);
+        const float iom = __builtin_amdgcn_rcpf(1.f - al);
+        T = inc ? T * iom : T;
+        const float wgt = inc ? al * T : 0.f;
+        const float cg = g0 * c4.x + g1 * c4.y + g2 * c4.z;
+        const float ga = T * cg - S * iom;
+        S += wgt * cg;
+        const uint64_t cm = __builtin_amdgcn_ballot_w64(act);
+        if (cm == 0) continue;
+        float pv[9];
+        const float wa = act ? wgt : 0.f;
+        pv[6] = wa * g0;
+        pv[7] = wa * g1;
+        pv[8] = wa * g2;
+        // the clamped alpha has no gradient with respect to opacity or shape
+        const float gal = (act && G2 < op.alpha_max) ? ga * al : 0.f;
+        pv[5] = gal;
+        pv[0] = gal * dx;
+        pv[1] = gal * dy;
+        pv[2] = pv[0] * dx;
+        pv[3] = pv[0] * dy;
+        pv[4] = pv[1] * dy;
+        emit_partial<DET>(s_acc, part, pmask, at >> 4, base, g16, slot, cm, grp, row_sum9(pv, lane));
+      }
+    }
+    if (!DET) {
+      // Wave w adds chunk w's walked active entries to their records, seven
+      // entries of nine consecutive components at a time, so an entry's adds
+      // leave in one or two requests, and clears what it has read.
+      __syncthreads();
+      const int fl = fresh(lane);
+      const int fe = fl / kG2d, fc = fl - fe * kG2d;
+      const int kf = wv * kWave + fl;
+      uint64_t m = __ballot(!MASKED || s_r2[kf].w > 0.f);
+      uint64_t walked = 0;
 #pragma unroll
-        for (int u = 0; u < kBwdUnroll; ++u) {
-          const bool has = mine != 0;
-          const int hb = has ? 63 - (int)__builtin_clzll(mine) : 0;
-          mine &= ~(1ull << hb);
-          kk[u] = c * kWave + hb;
-          val[u] = has && base + (uint32_t)kk[u] - start < lst;
-        }
-        uint32_t tag[kBwdUnroll];
-        float4 q2[kBwdUnroll];
-        float ee[kBwdUnroll], G2[kBwdUnroll], dxs[kBwdUnroll], dys[kBwdUnroll];
-#pragma unroll
-        for (int u = 0; u < kBwdUnroll; ++u) {
-          tag[u] = s_idx[kk[u]];
-          const float4 r0 = s_r0[kk[u]], r1 = s_r1[kk[u]];
-          q2[u] = s_r2[kk[u]];
-          dxs[u] = (pxc - r0.x) - r0.z;
-          dys[u] = (pyc - r0.y) - r0.w;
-          ee[u] = r1.w - (r1.x * dxs[u] * dxs[u] + r1.y * dxs[u] * dys[u] + r1.z * dys[u] * dys[u]);
-          G2[u] = __builtin_amdgcn_exp2f(ee[u]);
-        }
-        float pv[kBwdUnroll][9];
-        bool contrib[kBwdUnroll];
-#pragma unroll
-        for (int u = 0; u < kBwdUnroll; ++u) {
-          // Branch-free per lane: a lane that skips the entry multiplies its
-          // partials by zero and keeps its transmittance; staged records are
-          // finite, so the zero products are zeros.  Transmittance in front of
-          // the entry, its partials, then its colour joins the suffix.
-          const bool inc = val[u] && ee[u] >= op.log2_alpha_min;
-          const bool act = inc && (tag[u] >> 31) != 0;
-          const float al = fminf(op.alpha_max, G2[u]);
-          const float iom = __builtin_amdgcn_rcpf(1.f - al);
-          T = inc ? T * iom : T;
-          const float wgt = inc ? al * T : 0.f;
-          const float4 c4 = q2[u];
-          const float4 r3 = s_r3[kk[u]];
-          const float ga = g0 * (T * c4.x - s0 * iom) + g1 * (T * c4.y - s1 * iom) + g2 * (T * c4.z - s2 * iom);
-          const float wa = act ? wgt : 0.f;
-          pv[u][6] = wa * g0;
-          pv[u][7] = wa * g1;
-          pv[u][8] = wa * g2;
-          // the clamped alpha has no gradient with respect to opacity or shape
-          const float gal = (act && G2[u] < op.alpha_max) ? ga * al : 0.f;
-          const float dx = dxs[u], dy = dys[u];
-          pv[u][5] = gal != 0.f ? gal * __builtin_amdgcn_rcpf(c4.w) : 0.f;
-          const float gq = -0.5f * gal;  // d alpha / d q with q = d^T conic d
-          pv[u][2] = gq * dx * dx;
-          pv[u][3] = 2.f * gq * dx * dy;
-          pv[u][4] = gq * dy * dy;
-          pv[u][0] = -2.f * gq * (r3.y * dx + r3.z * dy);
-          pv[u][1] = -2.f * gq * (r3.z * dx + r3.w * dy);
-          contrib[u] = act;
-          s0 += wgt * c4.x;
-          s1 += wgt * c4.y;
-          s2 += wgt * c4.z;
-        }
-#pragma unroll
-        for (int u = 0; u < kBwdUnroll; ++u) {
-          const uint64_t cm = __ballot(contrib[u]);
-          if (cm != 0) {
-            const Sum9 r = row_sum9(pv[u], lane);
-            // the row's entries are shared by its 16 lanes, so the tags are row-uniform
-            emit_partial<DET>(g2d, part, pmask, tag[u], base + (uint32_t)kk[u], g16, slot, cm, grp, r);
-          }
-        }
+      for (int q = 0; q < kBlock / kWave; ++q) walked |= s_walk[wv][q];
+      m &= uniform_u64(walked);
+      const int cnt = (int)__popcll(m);
+      if ((m >> fl) & 1ull) s_list[wv][__popcll(m & ((1ull << fl) - 1ull))] = (uint8_t)fl;
+#pragma unroll 1
+      for (int e = fe < kWave / kG2d ? fe : kWave; e < cnt; e += kWave / kG2d) {
+        const int k = wv * kWave + (int)s_list[wv][e];
+        float* ap = s_acc + k * kG2d;
+        const float x = ap[fc], y = ap[fc ^ (fc < 2 ? 1 : 0)];
+        ap[fc] = 0.f;
+        const float4 r1 = s_r1[k];
+        const float val = g2d_component(fc, x, y, r1.x, r1.y, r1.z, fabsf(s_r2[k].w));
+        if (val != 0.f) atomicAdd(g2d + (int64_t)s_idx[k] * kG2d + fc, val);
       }
     }
     top = base;
@@ -1024,8 +1128,8 @@ __global__ __launch_bounds__(kBlock) void k_det_tile(const uint32_t* __restrict_
 }
 
 // Step 2, one thread per record: its pairs' sums in emission order (tiles of
-// its box row-major), added to the record's 2D gradient.
-__global__ __launch_bounds__(kBlock) void k_det_record(const int32_t* __restrict__ bin,
+// its box row-major), converted to the record's 2D gradient and added to it.
+__global__ __launch_bounds__(kBlock) void k_det_record(const int32_t* __restrict__ bin, const float* __restrict__ rec,
                                                        const uint32_t* __restrict__ offsets,
                                                        const float* __restrict__ tpart, float* __restrict__ g2d,
                                                        int64_t nrec, int64_t n_isect) {
@@ -1042,8 +1146,11 @@ __global__ __launch_bounds__(kBlock) void k_det_record(const int32_t* __restrict
 #pragma unroll
     for (int c = 0; c < kG2d; ++c) acc[c] += tpart[(e0 + k) * kG2d + c];
   }
+  const float4* R4 = reinterpret_cast<const float4*>(rec + r * kRecFloats);
+  const float4 r1 = R4[1];
+  const float op = R4[2].w;
 #pragma unroll
-  for (int c = 0; c < kG2d; ++c) g2d[r * kG2d + c] += acc[c];
+  for (int c = 0; c < kG2d; ++c) g2d[r * kG2d + c] += g2d_component(c, acc[c], acc[c < 2 ? 1 - c : c], r1.x, r1.y, r1.z, op);
 }
 
 size_t det_ws_bytes(int64_t n_isect) {
@@ -1195,8 +1302,8 @@ int32_t gs_render_backward_pixels_det(const gs_projected_t* proj, const uint32_t
   const int64_t nrec = (int64_t)V * n;
   hipLaunchKernelGGL(k_det_tile, dim3((unsigned)vs.tiles_total), dim3(kBlock), 0, s, vals, ranges, proj->bin,
                      proj->rec, proj->tile_cull_log2_alpha, offsets, part, pmask, tpart, nrec, n_isect, vs);
-  hipLaunchKernelGGL(k_det_record, dim3(grid_1d(nrec)), dim3(kBlock), 0, s, proj->bin, offsets, tpart, grad2d, nrec,
-                     n_isect);
+  hipLaunchKernelGGL(k_det_record, dim3(grid_1d(nrec)), dim3(kBlock), 0, s, proj->bin, proj->rec, offsets, tpart,
+                     grad2d, nrec, n_isect);
   MS_CHECK_LAUNCH("deterministic reduction");
   return GS_OK;
 }
