@@ -22,8 +22,8 @@
  *    buffer and an event for its read-back, made on first use and kept until
  *    the process ends.)
  *  - Asynchrony: work is enqueued on `stream` (a hipStream_t; NULL = the null
- *    stream).  Only gs_bin_count and gs_bin synchronise (they return the pair
- *    count).
+ *    stream).  Only gs_bin_count, gs_bin_tiles and gs_bin synchronise (they
+ *    return the pair count).
  *  - Reentrancy: no global mutable state (apart from the diagnostics
  *    gs_sort_set_spin_limit, gs_sort_set_algorithm and
  *    gs_bin_count_set_fold_blocks, and the scratch array of
@@ -152,6 +152,8 @@ typedef struct {
   int32_t tiles_total; /* sum over views of tiles_x * tiles_y */
   int32_t depth_bits;  /* bits kept of (zbits - zbits_min) in the sort key */
   int32_t key_bits;    /* significant bits of the sort key: tile bits + depth_bits */
+  int32_t max_list;    /* longest tile list, where the pairs were counted by tile (gs_bin_tiles, gs_bin), else 0 */
+  int32_t list_slices; /* slices that the longer of those lists are sorted in */
   int32_t pad;
 } gs_bin_stats_t;
 
@@ -233,9 +235,27 @@ int32_t gs_bin_sort(const gs_projected_t* proj, const gs_camera_t* cams, int32_t
                     const uint32_t* offsets, const gs_bin_stats_t* stats, uint64_t* keys, uint32_t* vals,
                     uint32_t* ranges, uint32_t* tile_order, void* ws, size_t ws_bytes, void* stream);
 
-/* a2-a4 in one call: gs_bin_count, then gs_bin_sort when the pairs fit the
+/* a2-a4 in two halves around the pair count, which the caller needs to size
+ * the lists.  gs_bin_tiles: what gs_bin_count returns, and the pairs counted
+ * by tile: ranges [dev, u32 tiles_total][2] holds what gs_bin_lists needs of
+ * them, tile_order [dev, u32 tiles_total] is final.  gs_bin_lists: vals, keys
+ * (may be NULL), ranges and tile_order as gs_bin_sort gives them, from the
+ * same proj, cameras, offsets, stats, ranges, tile_order and count workspace,
+ * left as gs_bin_tiles left them.  With tile_order NULL, with the look-back sort selected
+ * (gs_sort_set_algorithm) or with very long lists the radix sort of
+ * gs_bin_sort makes the lists; the results are the same.  gs_sort_status reads
+ * sort_ws.  gs_bin_tiles synchronises `stream`. */
+int32_t gs_bin_tiles(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
+                     gs_bin_stats_t* stats, uint32_t* ranges, uint32_t* tile_order, void* count_ws,
+                     size_t count_ws_bytes, void* stream);
+int32_t gs_bin_lists(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n,
+                     const uint32_t* offsets, const gs_bin_stats_t* stats, uint64_t* keys, uint32_t* vals,
+                     uint32_t* ranges, uint32_t* tile_order, void* count_ws, size_t count_ws_bytes, void* sort_ws,
+                     size_t sort_ws_bytes, void* stream);
+
+/* a2-a4 in one call: gs_bin_tiles, then gs_bin_lists when the pairs fit the
  * caller's buffers, with nothing between the pair count's read-back and the
- * sort's first launch (a caller that keeps its buffers from step to step
+ * lists' first launch (a caller that keeps its buffers from step to step
  * then pays one host round trip per binning).  Arguments as in the two calls;
  * pair_capacity = entries of vals (and of keys, when not NULL); ranges and
  * tile_order hold tiles_total entries (fixed by the cameras); count_ws /
@@ -243,8 +263,8 @@ int32_t gs_bin_sort(const gs_projected_t* proj, const gs_camera_t* cams, int32_t
  * status, with one addition: GS_ERR_CAPACITY with *stats and offsets valid
  * and stats->n_isect < 2^30 means the pairs did not fit (n_isect >
  * pair_capacity, or sort_ws_bytes < gs_bin_sort_workspace_size(n_isect));
- * nothing was sorted, and the caller grows its buffers and calls gs_bin_sort
- * with the same stats and offsets.  Synchronises `stream` (the pair count). */
+ * nothing was sorted, and the caller grows its buffers and calls gs_bin_lists
+ * (or gs_bin_sort) with the same stats and offsets.  Synchronises `stream` (the pair count). */
 int32_t gs_bin(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
                gs_bin_stats_t* stats, uint64_t* keys, uint32_t* vals, int64_t pair_capacity, uint32_t* ranges,
                uint32_t* tile_order, void* count_ws, size_t count_ws_bytes, void* sort_ws, size_t sort_ws_bytes,

@@ -51,7 +51,8 @@ class Projected(ctypes.Structure):
 
 class BinStats(ctypes.Structure):
     _fields_ = [("n_isect", c_i64), ("n_visible", c_i64), ("zbits_min", c_u32), ("zbits_max", c_u32),
-                ("tiles_total", c_i32), ("depth_bits", c_i32), ("key_bits", c_i32), ("pad", c_i32)]
+                ("tiles_total", c_i32), ("depth_bits", c_i32), ("key_bits", c_i32), ("max_list", c_i32),
+                ("list_slices", c_i32), ("pad", c_i32)]
 
 
 class FwdOut(ctypes.Structure):
@@ -83,6 +84,9 @@ _SIGS = {
     "gs_bin_sort_workspace_size": (c_sz, [c_i64]),
     "gs_bin_sort": (c_i32, [P(Projected), P(Camera), c_i32, c_i64, c_p, P(BinStats), c_p, c_p, c_p, c_p, c_p, c_sz,
                             c_p]),
+    "gs_bin_tiles": (c_i32, [P(Projected), P(Camera), c_i32, c_i64, c_p, P(BinStats), c_p, c_p, c_p, c_sz, c_p]),
+    "gs_bin_lists": (c_i32, [P(Projected), P(Camera), c_i32, c_i64, c_p, P(BinStats), c_p, c_p, c_p, c_p, c_p, c_sz,
+                             c_p, c_sz, c_p]),
     "gs_bin": (c_i32, [P(Projected), P(Camera), c_i32, c_i64, c_p, P(BinStats), c_p, c_p, c_i64, c_p, c_p, c_p, c_sz,
                        c_p, c_sz, c_p]),
     "gs_tile_order_workspace_size": (c_sz, []),

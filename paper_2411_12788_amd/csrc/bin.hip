@@ -1,4 +1,5 @@
-// a2-a4: tile binning.  Exclusive scan of tiles_touched, emission of one
+// a2-a4: tile binning (the general path; the lists of ordinary scenes are made
+// by tile, see tiles.hip).  Exclusive scan of tiles_touched, emission of one
 // (tile | depth) key per (tile, record) pair, stable LSD radix sort on the
 // significant key bits only (sort.hip), and per-tile [start, end) ranges.
 //
@@ -9,6 +10,7 @@
 // Subtracting a constant keeps the unsigned order of the float bits, which for
 // positive depths is the float order.
 #include "common.hpp"
+#include "tiles.hpp"
 
 #include <immintrin.h>
 
@@ -535,7 +537,8 @@ static int64_t count_blocks(int64_t nrec) { return (nrec + kScanTile - 1) / kSca
 
 size_t count_ws_size(int64_t nrec) {
   const int64_t nb = count_blocks(nrec > 0 ? nrec : 1);
-  return align256(nb * 8) + 3 * align256(nb * 4) + align256(64);
+  const size_t scan = align256(nb * 8) + 3 * align256(nb * 4) + align256(64), tiles = tile_ws_bytes(nrec);
+  return scan > tiles ? scan : tiles;
 }
 
 static CountWs carve_count(void* ws, int64_t nrec) {
@@ -554,6 +557,8 @@ static CountWs carve_count(void* ws, int64_t nrec) {
 size_t onesweep_ws_size(int64_t n, int32_t passes);
 int32_t onesweep_sort(uint64_t* k0, uint32_t* v0, int64_t n, int32_t lo_bit, int32_t bits, void* ws, uint32_t* vfinal,
                       uint64_t** keys_sorted, hipStream_t st);
+
+bool sort_is_prescan();
 
 size_t sort_ws_size(int64_t n) { return sort_ws_bytes(n); }
 
@@ -629,7 +634,7 @@ using namespace msplat;
 extern "C" {
 
 // The pair count's read-back.  The kernel that publishes the statistics
-// (k_count_down's last block, or k_count_top) also writes the four totals
+// (k_count_down's last block, k_count_top or k_tile_scan) also writes the totals
 // into a small host-mapped pinned buffer (one per host thread and device,
 // made on first use and kept until the process ends), and the host polls an
 // event recorded after the count instead of waiting in the runtime: a copy
@@ -637,9 +642,10 @@ extern "C" {
 // and the runtime's wait turns into an interrupt-driven sleep after a short
 // spin; both added tens of microseconds to a read-back that sits on the
 // step's critical path.
+constexpr uint64_t kUnsetTotal = ~0ull;
 struct CountReadback {
   hipEvent_t ev = nullptr;
-  uint64_t* host = nullptr;  // [4], host-mapped
+  uint64_t* host = nullptr;  // [8], host-mapped
   uint64_t* dev = nullptr;   // the same memory, as the device sees it
 };
 
@@ -672,8 +678,41 @@ int64_t gs_bin_count_set_fold_blocks(int64_t blocks) {
   return g_count_fold_blocks.exchange(blocks < 0 ? kCountFoldBlocks : blocks);
 }
 
-int32_t gs_bin_count(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
-                     gs_bin_stats_t* stats, void* ws, size_t ws_bytes, void* stream) {
+// Waits for the totals that a counting kernel queued on `s` writes to rb (the
+// first `words` of them; `fallback` holds them in device memory).
+static int32_t wait_totals(CountReadback* rb, hipStream_t s, const uint64_t* fallback, int words, uint64_t* h) {
+  int32_t st;
+  for (;;) {
+    const hipError_t e = hipEventQuery(rb->ev);
+    if (e == hipSuccess) break;
+    if (e != hipErrorNotReady) return check_hip(e, "bin_count wait");
+    _mm_pause();
+  }
+  for (int k = 0; k < words; ++k) h[k] = __atomic_load_n(rb->host + k, __ATOMIC_ACQUIRE);
+  if (h[0] == kUnsetTotal) {
+    st = check_hip(hipMemcpyAsync(h, fallback, words * sizeof(uint64_t), hipMemcpyDeviceToHost, s), "bin_count copy");
+    if (st != GS_OK) return st;
+    if ((st = check_hip(hipStreamSynchronize(s), "bin_count sync")) != GS_OK) return st;
+  }
+  return GS_OK;
+}
+
+static int32_t fill_stats(const ViewSet& vs, const uint64_t* h, gs_bin_stats_t* stats) {
+  stats->n_isect = (int64_t)h[0];
+  stats->n_visible = (int64_t)h[1];
+  stats->zbits_min = (uint32_t)h[2];
+  stats->zbits_max = (uint32_t)h[3];
+  stats->depth_bits = bits_for((uint64_t)(stats->zbits_max - stats->zbits_min));
+  stats->key_bits = stats->depth_bits + bits_for((uint64_t)(vs.tiles_total - 1));
+  if (h[0] >= (uint64_t)kSortMaxPairs) { set_error("pair count of 2^30 or more (sort limit)"); return GS_ERR_CAPACITY; }
+  return GS_OK;
+}
+
+// gs_bin_count, and (ranges not NULL) the pairs counted by tile where that
+// path applies.
+static int32_t bin_count(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
+                         gs_bin_stats_t* stats, uint32_t* ranges, uint32_t* tile_order, void* ws, size_t ws_bytes,
+                         void* stream) {
   if (!proj || !stats) { set_error("proj/stats NULL"); return GS_ERR_NULL; }
   ViewSet vs;
   int32_t st = build_views(cams, V, &vs);
@@ -690,12 +729,25 @@ int32_t gs_bin_count(const gs_projected_t* proj, const gs_camera_t* cams, int32_
   hipStream_t s = (hipStream_t)stream;
   CountReadback* rb = nullptr;
   if ((st = count_readback(&rb)) != GS_OK) return st;
-  CountWs c = carve_count(ws, nrec);
-  c.host_stats = rb->dev;
   // a value no count can produce: if it were still there after the wait, the
   // totals come from the device copy instead
-  constexpr uint64_t kUnset = ~0ull;
-  __atomic_store_n(rb->host, kUnset, __ATOMIC_RELEASE);
+  __atomic_store_n(rb->host, kUnsetTotal, __ATOMIC_RELEASE);
+  uint64_t h[kTileStats];
+  if (ranges && tile_order && sort_is_prescan() && tiles_eligible(vs) &&
+      (proj->rec || !(proj->tile_cull_log2_alpha < 0.f))) {
+    const TileWs t = carve_tiles(ws, nrec);
+    if ((st = count_by_tile(proj, vs, V, n, ranges, t, rb->dev, s)) != GS_OK) return st;
+    if ((st = check_hip(hipEventRecord(rb->ev, s), "bin_count event")) != GS_OK) return st;
+    // runs while the totals travel to the host
+    if ((st = offsets_by_tile(proj, vs, V, n, t, offsets, tile_order, s)) != GS_OK) return st;
+    if ((st = wait_totals(rb, s, t.stats, kTileStats, h)) != GS_OK) return st;
+    if ((st = fill_stats(vs, h, stats)) != GS_OK) return st;
+    stats->max_list = (int32_t)h[4];
+    stats->list_slices = (int32_t)h[5];
+    return GS_OK;
+  }
+  CountWs c = carve_count(ws, nrec);
+  c.host_stats = rb->dev;
   const int64_t nb = count_blocks(nrec);
   const int4* bin = reinterpret_cast<const int4*>(proj->bin);
   hipLaunchKernelGGL(k_count_reduce, dim3((unsigned)nb), dim3(kBlock), 0, s, bin, nrec, c);
@@ -707,27 +759,19 @@ int32_t gs_bin_count(const gs_projected_t* proj, const gs_camera_t* cams, int32_
   }
   MS_CHECK_LAUNCH("bin_count");
   if ((st = check_hip(hipEventRecord(rb->ev, s), "bin_count event")) != GS_OK) return st;
-  for (;;) {
-    const hipError_t e = hipEventQuery(rb->ev);
-    if (e == hipSuccess) break;
-    if (e != hipErrorNotReady) return check_hip(e, "bin_count wait");
-    _mm_pause();
-  }
-  uint64_t h[4];
-  for (int k = 0; k < 4; ++k) h[k] = __atomic_load_n(rb->host + k, __ATOMIC_ACQUIRE);
-  if (h[0] == kUnset) {
-    st = check_hip(hipMemcpyAsync(h, c.stats, sizeof(h), hipMemcpyDeviceToHost, s), "bin_count copy");
-    if (st != GS_OK) return st;
-    if ((st = check_hip(hipStreamSynchronize(s), "bin_count sync")) != GS_OK) return st;
-  }
-  stats->n_isect = (int64_t)h[0];
-  stats->n_visible = (int64_t)h[1];
-  stats->zbits_min = (uint32_t)h[2];
-  stats->zbits_max = (uint32_t)h[3];
-  stats->depth_bits = bits_for((uint64_t)(stats->zbits_max - stats->zbits_min));
-  stats->key_bits = stats->depth_bits + bits_for((uint64_t)(vs.tiles_total - 1));
-  if (h[0] >= (uint64_t)kSortMaxPairs) { set_error("pair count of 2^30 or more (sort limit)"); return GS_ERR_CAPACITY; }
-  return GS_OK;
+  if ((st = wait_totals(rb, s, c.stats, 4, h)) != GS_OK) return st;
+  return fill_stats(vs, h, stats);
+}
+
+int32_t gs_bin_count(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
+                     gs_bin_stats_t* stats, void* ws, size_t ws_bytes, void* stream) {
+  return bin_count(proj, cams, V, n, offsets, stats, nullptr, nullptr, ws, ws_bytes, stream);
+}
+
+int32_t gs_bin_tiles(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
+                     gs_bin_stats_t* stats, uint32_t* ranges, uint32_t* tile_order, void* count_ws,
+                     size_t count_ws_bytes, void* stream) {
+  return bin_count(proj, cams, V, n, offsets, stats, ranges, tile_order, count_ws, count_ws_bytes, stream);
 }
 
 size_t gs_sort_workspace_size(int64_t n) { return sort_ws_size(n); }
@@ -811,19 +855,47 @@ int32_t gs_bin_sort(const gs_projected_t* proj, const gs_camera_t* cams, int32_t
   if (ws_bytes < gs_bin_sort_workspace_size(ni)) { set_error("bin_sort workspace too small"); return GS_ERR_CAPACITY; }
   return bin_sort_on_ws(proj, vs, V, n, offsets, stats, keys, vals, ranges, tile_order, ws, s);
 }
+
+int32_t gs_bin_lists(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n,
+                     const uint32_t* offsets, const gs_bin_stats_t* stats, uint64_t* keys, uint32_t* vals,
+                     uint32_t* ranges, uint32_t* tile_order, void* count_ws, size_t count_ws_bytes, void* sort_ws,
+                     size_t sort_ws_bytes, void* stream) {
+  if (!stats || stats->n_isect <= 0 || !tile_order || !lists_by_tile_pay(stats))
+    return gs_bin_sort(proj, cams, V, n, offsets, stats, keys, vals, ranges, tile_order, sort_ws, sort_ws_bytes,
+                       stream);
+  if (!proj) { set_error("proj/stats NULL"); return GS_ERR_NULL; }
+  ViewSet vs;
+  int32_t st = build_views(cams, V, &vs);
+  if (st != GS_OK) return st;
+  if ((st = check_records(V, n)) != GS_OK) return st;
+  if (stats->tiles_total != vs.tiles_total) { set_error("stats do not match cameras"); return GS_ERR_SHAPE; }
+  if (!ranges) { set_error("ranges NULL"); return GS_ERR_NULL; }
+  if (!count_ws || !sort_ws) { set_error("workspace NULL"); return GS_ERR_NULL; }
+  if (!vals || !offsets || !proj->bin) { set_error("buffer NULL"); return GS_ERR_NULL; }
+  if (proj->tile_cull_log2_alpha < 0.f && !proj->rec) { set_error("tile culling needs proj->rec"); return GS_ERR_NULL; }
+  if (count_ws_bytes < count_ws_size((int64_t)V * n)) { set_error("count workspace too small"); return GS_ERR_CAPACITY; }
+  if (stats->n_isect >= kSortMaxPairs) { set_error("pair count of 2^30 or more (sort limit)"); return GS_ERR_CAPACITY; }
+  if (sort_ws_bytes < gs_bin_sort_workspace_size(stats->n_isect)) {
+    set_error("bin_sort workspace too small");
+    return GS_ERR_CAPACITY;
+  }
+  return lists_by_tile(proj, vs, V, n, stats, carve_tiles(count_ws, (int64_t)V * n), ranges, keys, vals, sort_ws,
+                       (hipStream_t)stream);
+}
+
 int32_t gs_bin(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
                gs_bin_stats_t* stats, uint64_t* keys, uint32_t* vals, int64_t pair_capacity, uint32_t* ranges,
                uint32_t* tile_order, void* count_ws, size_t count_ws_bytes, void* sort_ws, size_t sort_ws_bytes,
                void* stream) {
   if (pair_capacity < 0) { set_error("pair_capacity < 0"); return GS_ERR_SHAPE; }
-  int32_t st = gs_bin_count(proj, cams, V, n, offsets, stats, count_ws, count_ws_bytes, stream);
+  int32_t st = gs_bin_tiles(proj, cams, V, n, offsets, stats, ranges, tile_order, count_ws, count_ws_bytes, stream);
   if (st != GS_OK) return st;
   if (stats->n_isect > pair_capacity || sort_ws_bytes < gs_bin_sort_workspace_size(stats->n_isect)) {
-    set_error("the pairs do not fit the buffers: grow them to stats->n_isect and call gs_bin_sort");
+    set_error("the pairs do not fit the buffers: grow them to stats->n_isect and call gs_bin_lists");
     return GS_ERR_CAPACITY;
   }
-  return gs_bin_sort(proj, cams, V, n, offsets, stats, keys, vals, ranges, tile_order, sort_ws, sort_ws_bytes,
-                     stream);
+  return gs_bin_lists(proj, cams, V, n, offsets, stats, keys, vals, ranges, tile_order, count_ws, count_ws_bytes,
+                      sort_ws, sort_ws_bytes, stream);
 }
 
 size_t gs_tile_order_workspace_size(void) { return 256; }

@@ -366,6 +366,8 @@ int32_t launch_fill(void* dst, uint32_t value, int64_t count, hipStream_t st);
 static std::atomic<uint32_t> g_spin_limit{1u << 22};
 static std::atomic<int32_t> g_sort_algorithm{GS_SORT_PRESCAN};
 
+bool sort_is_prescan() { return g_sort_algorithm.load() == GS_SORT_PRESCAN; }
+
 // Sorts (k0, v0) on key bits [lo_bit, lo_bit + bits); the last pass writes
 // values to vfinal and keys to the buffer returned in *keys_sorted (k0 or the
 // workspace copy).  With v0 == NULL only the keys are sorted (vfinal unused).

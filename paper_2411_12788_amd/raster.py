@@ -298,8 +298,9 @@ def bin_step(proj: Projected, cams, n: int, buffers: StepBuffers, want_keys: boo
         on_count(st)
     if grow:
         vals, keys, ranges, order, ws = bb.get(ni, tiles, want_keys, dev)
-        L.check(lib.gs_bin_sort(ctypes.byref(pc), cc, V, n, _ptr(offsets), ctypes.byref(st), _ptr(keys), _ptr(vals),
-                                _ptr(ranges), _ptr(order), _ptr(ws), ws.numel(), sp), "gs_bin_sort")
+        L.check(lib.gs_bin_lists(ctypes.byref(pc), cc, V, n, _ptr(offsets), ctypes.byref(st), _ptr(keys), _ptr(vals),
+                                 _ptr(ranges), _ptr(order), _ptr(cws), cws.numel(), _ptr(ws), ws.numel(), sp),
+                "gs_bin_lists")
     else:
         L.check(rc, "gs_bin")
     return Binned(bb.vals[:ni], bb.ranges[: 2 * tiles].view(tiles, 2), bb.keys[:ni] if want_keys else None, st,
@@ -314,11 +315,10 @@ def sort_status(ws: torch.Tensor, stream=None) -> None:
 def bin(proj: Projected, cams, n: int, want_keys: bool = False, stream=None, check: bool = True) -> Binned:
     """Pair count, key emission, sort and ranges; with `check` the sort's
     status flag is read back (one synchronisation)."""
-    offsets, st = bin_count(proj, cams, n, stream)
-    buffers = BinBuffers()
-    out = bin_sort(proj, cams, n, offsets, st, want_keys, stream, buffers)
+    buffers = StepBuffers()
+    out = bin_step(proj, cams, n, buffers, want_keys, stream)
     if check:
-        sort_status(buffers.ws, stream)
+        sort_status(buffers.bins.ws, stream)
     return out
 
 
