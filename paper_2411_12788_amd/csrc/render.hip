@@ -9,16 +9,17 @@
 // up to 256 consecutive list entries (record index, pixel box and the 48 or
 // 64 bytes of the record the pass reads) in LDS with one gather per thread,
 // while the next round's records and the list indices of the round after are
-// already in flight.  Each lane then tests one staged entry against the
-// bounding rectangle of each group's still-active pixels (pixel box, then an
-// exact conservative ellipse-rectangle test), the ballots give every group its
-// own stream of entries that can reach it (LDS offsets, written by the lanes
-// that tested them), and each group walks its stream in list order reading
-// records with broadcast LDS loads.  Culled entries never
-// reach alpha_min at those pixels, so culling never changes a result.  Groups
-// whose pixels have all stopped drop the rest of their stream, and a wave ends
-// when all its groups have.
+// already in flight.  Each thread then tests the entry it staged against the
+// bounding rectangle of the still-active pixels of every group of the
+// workgroup (pixel box, then an exact conservative ellipse-rectangle test); the
+// ballots, expanded by each wave for its own groups, give every group its own
+// stream of entries that can reach it (LDS offsets), and each group walks its
+// stream in list order reading records with broadcast LDS loads.  Culled
+// entries never reach alpha_min at those pixels, so culling never changes a
+// result.  Groups whose pixels have all stopped drop the rest of their stream,
+// and a wave ends when all its groups have.
 #include <cmath>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -68,48 +69,64 @@ __device__ __noinline__ MidDepth mid_depth(const RayCam cam, const float* __rest
   const double d2 = R[2] * e0 + R[5] * e1 + R[8];
   const double qw = quats[g], qx = quats[n + g], qy = quats[2 * n + g], qz = quats[3 * n + g];
   const double iq = 1.0 / sqrt(qw * qw + qx * qx + qy * qy + qz * qz);
-  const double w = qw * iq, x = qx * iq, y = qy * iq, z = qz * iq;
-  const double Q[3][3] = {{1.0 - 2.0 * (y * y + z * z), 2.0 * (x * y - w * z), 2.0 * (x * z + w * y)},
-                          {2.0 * (x * y + w * z), 1.0 - 2.0 * (x * x + z * z), 2.0 * (y * z - w * x)},
-                          {2.0 * (x * z - w * y), 2.0 * (y * z + w * x), 1.0 - 2.0 * (x * x + y * y)}};
-  const double o0 = c0 - means[g], o1 = c1 - means[n + g], o2 = c2 - means[2 * n + g];
+  double w = qw * iq, x = qx * iq, y = qy * iq, z = qz * iq;
+  double o0 = c0 - means[g], o1 = c1 - means[n + g], o2 = c2 - means[2 * n + g];
   double od = 0.0, dd = 0.0, oo = 0.0;
-  for (int k = 0; k < 3; ++k) {
-    const double is = 1.0 / (double)scales[k * n + g];
-    const double ok = (Q[0][k] * o0 + Q[1][k] * o1 + Q[2][k] * o2) * is;
-    const double dk = (Q[0][k] * d0 + Q[1][k] * d1 + Q[2][k] * d2) * is;
+  // One axis of the ellipsoid (a column of its rotation) after the other: side
+  // by side they take 72 registers, more than the kernels that call this.
+  auto axis = [&](double q0, double q1, double q2, float scale) {
+    const double is = 1.0 / (double)scale;
+    const double ok = (q0 * o0 + q1 * o1 + q2 * o2) * is;
+    const double dk = (q0 * d0 + q1 * d1 + q2 * d2) * is;
     od += ok * dk;
     dd += dk * dk;
     oo += ok * ok;
-  }
+    asm volatile("" : "+v"(od), "+v"(dd), "+v"(oo), "+v"(w), "+v"(x), "+v"(y), "+v"(z));
+  };
+  axis(1.0 - 2.0 * (y * y + z * z), 2.0 * (x * y + w * z), 2.0 * (x * z - w * y), scales[g]);
+  axis(2.0 * (x * y - w * z), 1.0 - 2.0 * (x * x + z * z), 2.0 * (y * z + w * x), scales[n + g]);
+  axis(2.0 * (x * z + w * y), 2.0 * (y * z - w * x), 1.0 - 2.0 * (x * x + y * y), scales[2 * n + g]);
   MidDepth r;
   r.depth = (float)(-od / dd);
   r.hit = (od * od - dd * (oo - 1.0)) >= 0.0 ? 1u : 0u;
   return r;
 }
 
-// Wave-wide sum / max of one float, result uniform (read from lane 63).
-// Butterfly inside each 16-lane row through DPP (quad xor 1, quad xor 2,
-// half-row mirror, row mirror), then rows combined with the row broadcasts.
-template <bool MAX>
-__device__ __forceinline__ float dpp_combine(float a, float b) { return MAX ? fmaxf(a, b) : a + b; }
-
-template <bool MAX>
-__device__ __forceinline__ float wave_reduce_dpp(float x) {
-  const int ident = MAX ? 0 : 0;  // inputs are >= 0 for MAX, so 0 is an identity for both
-  x = dpp_combine<MAX>(x, __int_as_float(__builtin_amdgcn_update_dpp(ident, __float_as_int(x), 0xB1, 0xF, 0xF, false)));
-  x = dpp_combine<MAX>(x, __int_as_float(__builtin_amdgcn_update_dpp(ident, __float_as_int(x), 0x4E, 0xF, 0xF, false)));
-  x = dpp_combine<MAX>(x, __int_as_float(__builtin_amdgcn_update_dpp(ident, __float_as_int(x), 0x141, 0xF, 0xF, false)));
-  x = dpp_combine<MAX>(x, __int_as_float(__builtin_amdgcn_update_dpp(ident, __float_as_int(x), 0x140, 0xF, 0xF, false)));
-  x = dpp_combine<MAX>(x, __int_as_float(__builtin_amdgcn_update_dpp(ident, __float_as_int(x), 0x142, 0xA, 0xF, false)));
-  x = dpp_combine<MAX>(x, __int_as_float(__builtin_amdgcn_update_dpp(ident, __float_as_int(x), 0x143, 0xC, 0xF, false)));
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
-}
-
 // Value of another lane of the same 16-lane row (DPP control CTRL).
 template <int CTRL>
 __device__ __forceinline__ float dpp_take(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+// Sum and largest of two weights (>= 0) per lane over each 16-lane row, the
+// first's in lanes 0-7 of a row, the second's in lanes 8-15 (the bank masks of
+// the first adds keep one in either half, see row_sum9).  The accumulating
+// forward then adds an entry's weights from one lane per group.
+// Adding every lane's weight in LDS instead cost up to 240 cycles of the CU's
+// LDS per entry (ds_add_f32 takes one lane at a time) and 60 for the maximum
+// (lanes of one address take turns): three times the vector instructions of
+// the walk.
+struct SumMax {
+  float sum, max;
+};
+__device__ __forceinline__ SumMax row_sum_max2(float w0, float w1) {
+  SumMax r;
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_max_f32_dpp %1, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_max_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+      : "=&v"(r.sum), "=&v"(r.max)
+      : "v"(w0), "v"(w1));
+  return r;
 }
 // Exchanges between the four 16-lane rows of one column (lanes j, 16 + j,
 // 32 + j, 48 + j) with the gfx950 permlane swaps: permlane16_swap hands each
@@ -225,10 +242,22 @@ __device__ __forceinline__ Rect group_rect(uint32_t bits, int32_t gx0, int32_t g
   return r;
 }
 
+// The same value, which the compiler does not know to be the same: what is
+// computed from it is computed where it is used instead of being held in
+// registers over the loops in between (registers set how many waves a SIMD
+// holds in these kernels).
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ int32_t fresh_uniform(int32_t x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
 // One staged entry against the pixel centres of a group's rectangle: what
-// ellipse_meets decides, for the many tests of a chunk.  `ox`, `oy`: the centre
-// of the wave's first pixel minus the entry's mean; x0..y1: the rectangle,
-// from that pixel.  A convex quadratic with its minimum outside a rectangle
+// ellipse_meets decides, for the many tests of a round.  `ox`, `oy`: the centre
+// of the work item's first pixel minus the entry's mean; x0..y1: the
+// rectangle, from that pixel.  A convex quadratic with its minimum outside a rectangle
 // takes its least value there on one of the (at most two) edges that face the
 // minimum, so two edges are tried instead of four: the one at the nearest x
 // and the one at the nearest y (where the minimum lies between the edges, the
@@ -238,11 +267,11 @@ __device__ __forceinline__ Rect group_rect(uint32_t bits, int32_t gx0, int32_t g
 struct EntryTest {
   float ox, oy, A, B, C, hiA, hiC, lim;
 };
-__device__ __forceinline__ EntryTest entry_test(float4 r0, float4 r1, int32_t sx0, int32_t sy0,
+__device__ __forceinline__ EntryTest entry_test(float4 r0, float4 r1, int32_t ix0, int32_t iy0,
                                                 float log2_alpha_min) {
   EntryTest t;
-  t.ox = ((float)sx0 + 0.5f - r0.x) - r0.z;
-  t.oy = ((float)sy0 + 0.5f - r0.y) - r0.w;
+  t.ox = ((float)ix0 + 0.5f - r0.x) - r0.z;
+  t.oy = ((float)iy0 + 0.5f - r0.y) - r0.w;
   t.A = r1.x;
   t.B = r1.y;
   t.C = r1.z;
@@ -261,54 +290,158 @@ __device__ __forceinline__ bool group_meets(const EntryTest& t, float x0, float 
   return fminf(qx, qy) <= t.lim;
 }
 
-// Streams of a wave's four groups for one chunk of 64 staged entries: the LDS
-// byte offsets (16 per entry) of the entries that can reach the group, in list
-// order, with their counts.  Walking a list of offsets costs a 16-bit LDS read
-// per entry; walking the ballot masks instead costs ten vector instructions
-// per entry (two-word bit scans and clears per lane).
+// List entries staged per workgroup round, at most one per thread.  A round
+// costs its barriers and its streams whatever its length, so rounds are as long
+// as LDS allows at six workgroups per CU (26,880 bytes each): the backward's
+// double accumulators (72 bytes per entry) leave room for 192, its float ones
+// and the forms without accumulators for 256.
+constexpr int kFwdBatch = 256;
+template <bool MASKED, bool DET>
+constexpr int kBwdBatch = MASKED || DET ? 256 : 192;
+
+// The groups' streams of one round.  Every thread tests its staged entry, still
+// in registers, against all groups of the workgroup (four per wave, one per
+// wave in a split work item), so an entry's test is set up once instead of
+// once per wave, and the records need not be read back from LDS.  Wave c leaves
+// the ballots of its 64 entries in mask[wave][group][c]; after the barrier each
+// wave expands its own groups' masks into lists of entries.  Walking a list
+// costs one LDS read per entry (two per read in the forward); walking the masks
+// instead costs ten vector instructions per entry (two-word bit scans and
+// clears per lane), and walking 64 entries at a time waits for the slowest of
+// the four groups four times as often.
 constexpr int kGroups = 4;
-struct Streams {
-  int n[kGroups];
-  uint64_t any;  // entries in some stream
-};
-__device__ __forceinline__ Streams make_streams(uint16_t (*stream)[kWave], int2 box, float4 r0, float4 r1, bool in,
-                                                uint64_t active, int groups, int32_t sx0, int32_t sy0, int k, int lane,
-                                                float log2_alpha_min) {
-  Streams st;
-  st.any = 0;
-  const EntryTest t = entry_test(r0, r1, sx0, sy0, log2_alpha_min);
+constexpr int kWaves = kBlock / kWave;
+template <int BATCH>
+struct RoundLds {
+  static constexpr int chunks = BATCH / kWave;
+  uint64_t active[kWaves];                  // pixels of each wave that still composite
+  uint64_t mask[kWaves][kGroups][chunks];
+  __device__ __forceinline__ bool none_active() const {
+    uint64_t any = 0;
 #pragma unroll
-  for (int g = 0; g < kGroups; ++g) {
-    const uint32_t bits = g < groups ? (uint32_t)(active >> (16 * g)) & 0xffffu : 0u;
-    st.n[g] = 0;
-    if (bits != 0u) {
-      const Rect rg = group_rect(bits, sx0 + (g & 1) * 4, sy0 + (g >> 1) * 4);
-      const bool rel = in && box_meets(box, rg.x0, rg.x1, rg.y0, rg.y1) &&
-                       group_meets(t, (float)(rg.x0 - sx0), (float)(rg.x1 - sx0), (float)(rg.y0 - sy0),
-                                   (float)(rg.y1 - sy0));
-      const uint64_t m = __builtin_amdgcn_ballot_w64(rel);
-      if (rel) stream[g][__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
-          (uint16_t)(k * 16);
-      st.n[g] = (int)__popcll(m);
-      st.any |= m;
+    for (int w = 0; w < kWaves; ++w) any |= active[w];
+    return uniform_u64(any) == 0;
+  }
+};
+// `group_last` (or NULL): list positions from which on a group composites nothing.
+// Returns the entries of this wave's chunk that some group walks.
+template <int BATCH>
+__device__ __forceinline__ uint64_t test_round(RoundLds<BATCH>& s, const uint32_t* group_last, uint32_t pos, bool split,
+                                               int32_t ix0, int32_t iy0, int2 box, float4 r0, float4 r1, bool in,
+                                               int wv, int lane, float log2_alpha_min) {
+  if (wv >= RoundLds<BATCH>::chunks) return 0;
+  uint64_t any = 0;
+  uint32_t lo = 0, hi = 0;  // lane 4 w + g keeps the mask of group g of wave w
+  if (__builtin_amdgcn_ballot_w64(in) != 0) {
+    const EntryTest t = entry_test(r0, r1, ix0, iy0, log2_alpha_min);
+    uint32_t last = 0;
+    if (group_last) last = group_last[lane & (kWaves * kGroups - 1)];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const uint64_t am = uniform_u64(s.active[w]);
+#pragma unroll
+      for (int g = 0; g < kGroups; ++g) {
+        const uint32_t two = (uint32_t)(g < 2 ? am : am >> 32);
+        const uint32_t bits = split && g > 0 ? 0u : (g & 1) ? two >> 16 : two & 0xffffu;
+        if (bits == 0u) continue;
+        const int32_t gx = split ? (w & 1) * 4 : (w & 1) * 8 + (g & 1) * 4;
+        const int32_t gy = split ? (w >> 1) * 4 : (w >> 1) * 8 + (g >> 1) * 4;
+        const Rect rg = group_rect(bits, gx, gy);
+        bool rel = in && box_meets(box, ix0 + rg.x0, ix0 + rg.x1, iy0 + rg.y0, iy0 + rg.y1) &&
+                   group_meets(t, (float)rg.x0, (float)rg.x1, (float)rg.y0, (float)rg.y1);
+        if (group_last) rel = rel && pos < (uint32_t)__builtin_amdgcn_readlane((int)last, w * kGroups + g);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(rel);
+        // (a vector instruction may read a scalar two instructions after another has written it)
+        asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+            : "+v"(lo), "+v"(hi)
+            : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)), "n"(w * kGroups + g));
+        any |= m;
+      }
+    }
+  }
+  if (lane < kWaves * kGroups)
+    s.mask[lane / kGroups][lane & (kGroups - 1)][wv] = (uint64_t)lo | ((uint64_t)hi << 32);
+  return any;
+}
+// Entries of this wave's groups, `unit` per staged entry; n[g]: their counts.
+// By chunk, in a split work item: n[c] is where chunk c's part of the one
+// group's stream ends, filled up with kNoEntry to a multiple of four.
+constexpr uint16_t kNoEntry = 0xffff;
+__device__ __forceinline__ int fill_four(uint16_t* stream, int n, int lane) {
+  const int fill = -n & 3;
+  if (lane < fill) stream[n + lane] = kNoEntry;
+  return n + fill;
+}
+template <bool BY_CHUNK, typename T, int BATCH>
+__device__ __forceinline__ void make_streams(const RoundLds<BATCH>& s, T (*stream)[BATCH], int unit, bool split,
+                                             bool by_chunk, int wv, int lane, int (&n)[kGroups]) {
+  constexpr int kChunks = RoundLds<BATCH>::chunks;
+  static_assert(!BY_CHUNK || kChunks == kGroups, "n holds one end per chunk");
+  const uint64_t mine = (&s.mask[wv][0][0])[lane < kGroups * kChunks ? lane : 0];
+  auto put = [&](int g, int c, int at) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, g * kChunks + c);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), g * kChunks + c);
+    const uint64_t m = (uint64_t)lo | ((uint64_t)hi << 32);
+    if (__builtin_amdgcn_inverse_ballot_w64(m))
+      stream[g][at + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))] =
+          (T)((c * kWave + lane) * unit);
+    return (int)__popcll(m);
+  };
+  bool grouped = true;
+  if constexpr (BY_CHUNK) {
+    if (by_chunk) {
+      grouped = false;
+      int at = 0;
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) n[c] = at = fill_four(stream[0], at + put(0, c, at), lane);
+    }
+  }
+  if (grouped) {
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      n[g] = 0;
+      if (split && g > 0) continue;
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) n[g] += put(g, c, n[g]);
     }
   }
   // the lanes of this wave read what other lanes of it have written
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  return st;
-}
-// The same value, which the compiler does not know to be the same: what is
-// computed from it is computed where it is used instead of being held in
-// registers over the loops in between (registers set how many waves a SIMD
-// holds in these kernels).
-__device__ __forceinline__ int fresh(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 template <typename T>
 __device__ __forceinline__ T lds_at(const T* base, uint32_t bytes) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
+}
+
+// Row-parallel forward: of the entries in [from, until) of the stream, one
+// chunk's, those that meet the rectangle of the pixels `bits` of the group at
+// (gx, gy) move to its front, the rest becomes kNoEntry.
+__device__ __forceinline__ void retest_chunk(uint16_t* stream, int from, int until, const float4* s_r0,
+                                             const float4* s_r1, const float4* s_r2, const int32_t* __restrict__ bin,
+                                             uint32_t bits, int32_t ix0, int32_t iy0, int32_t gx, int32_t gy, int lane,
+                                             float log2_alpha_min) {
+  const bool slot = from + lane < until;
+  const uint32_t off = slot ? stream[from + lane] : kNoEntry;
+  bool rel = off != kNoEntry;
+  if (rel) {
+    const Rect rg = group_rect(bits, gx, gy);
+    const uint32_t r = __float_as_uint(lds_at(s_r2, off).w);  // a stream holds valid entries only
+    const int2 box = *reinterpret_cast<const int2*>(bin + 4 * (int64_t)r);
+    const EntryTest t = entry_test(lds_at(s_r0, off), lds_at(s_r1, off), ix0, iy0, log2_alpha_min);
+    rel = box_meets(box, ix0 + rg.x0, ix0 + rg.x1, iy0 + rg.y0, iy0 + rg.y1) &&
+          group_meets(t, (float)rg.x0, (float)rg.x1, (float)rg.y0, (float)rg.y1);
+  }
+  const uint64_t m = __builtin_amdgcn_ballot_w64(rel);
+  // each lane of a slot writes one: the entries in order, then the empty ones
+  const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  if (slot) stream[from + (rel ? below : (int)__popcll(m) + lane - below)] = (uint16_t)(rel ? off : kNoEntry);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ int max4(const int (&n)[kGroups]) {
+  const int a = n[0] > n[1] ? n[0] : n[1], b = n[2] > n[3] ? n[2] : n[3];
+  return a > b ? a : b;
 }
 
 // Work item of a render workgroup.  With a tile order (longest lists first),
@@ -415,7 +548,6 @@ inline int32_t split_tiles(const uint32_t* order, int32_t tiles_total) {
   return order ? t & ~7 : 0;
 }
 
-constexpr int kBatch = kBlock;  // list entries staged per workgroup round
 constexpr int kFwdUnroll = 2;   // entries of a group's stream per forward iteration
 static_assert(kFwdUnroll == 2, "an iteration's two 16-bit offsets come from one 32-bit read");
 constexpr uint32_t kNoOffset = 0xffffffffu, kNoRecord = 0xffffffffu;
@@ -431,9 +563,16 @@ __device__ __forceinline__ void set_wave_priority(uint32_t list_len) {
 
 // Forward.  Per round the workgroup gathers up to 256 consecutive list entries
 // (index, pixel box, 48-byte record) into LDS with one load per thread, so the
-// latency of the random record gathers is paid once per 256 entries.  Each wave
-// then ballots which staged entries touch its 8x8 quarter and walks only
-// those, reading the record with broadcast LDS loads.
+// latency of the random record gathers is paid once per 256 entries; all
+// threads test them against the workgroup's pixel groups (test_round), and
+// each wave walks the lists of its own groups with broadcast LDS loads.
+// Bound by the vector instructions of the walk, and under row-parallel
+// splitting by the latency of the longest lists.  Measured with the tests in
+// the staging thread, one list per round, the weights summed before they go to
+// LDS and 72 registers instead of 79 (seven waves per SIMD without
+// accumulation): 3M Gaussians at 1920x1080 with accumulation 599 -> 549 us and
+// without 340 -> 333 us, 100k at 637x479 with accumulation 126 -> 64 us, 4 views
+// of 1.5M 745 -> 707 us.
 template <bool ACC, bool OUT, int DEPTH>
 __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
                                                        const uint32_t* __restrict__ vals,
@@ -445,16 +584,18 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
                                                        int32_t per_view, ViewSet vs) {
   // s_r2[k].w carries the record index (the forward never reads the opacity
   // field), so one read returns colour and index
-  __shared__ float4 s_r0[kBatch], s_r1[kBatch], s_r2[kBatch];
-  __shared__ int2 s_box[kBatch];
-  __shared__ float s_z[DEPTH == GS_DEPTH_BLEND ? kBatch : 1];
+  __shared__ float4 s_r0[kFwdBatch], s_r1[kFwdBatch], s_r2[kFwdBatch];
+  __shared__ RoundLds<kFwdBatch> s_round;
+  __shared__ float s_z[DEPTH == GS_DEPTH_BLEND ? kFwdBatch : 1];
   // per staged entry: importance and max weight gathered from the whole
   // workgroup with LDS atomics, flushed with one global atomic per entry
-  __shared__ float s_acc_w[ACC ? kBatch : 1];
-  __shared__ uint32_t s_acc_m[ACC ? kBatch : 1];
-  __shared__ uint16_t s_stream[kBlock / kWave][kGroups][kWave];
+  // (double, and one lane per group: see row_sum_max2)
+  __shared__ double s_acc_w[ACC ? kFwdBatch : 1];
+  __shared__ uint32_t s_acc_m[ACC ? kFwdBatch : 1];
+  __shared__ uint16_t s_stream[kWaves][kGroups][kFwdBatch];
   // an offset read past a stream's end is unused, but it is read: keep it in range
-  for (int q = threadIdx.x; q < kBlock / kWave * kGroups * kWave; q += kBlock) (&s_stream[0][0][0])[q] = 0;
+  for (int q = threadIdx.x; q < kWaves * kGroups * kFwdBatch / 2; q += kBlock)
+    reinterpret_cast<uint32_t*>(&s_stream[0][0][0])[q] = 0;
   const WorkItem wi = work_item(order, ranges, nsplit, vs.tiles_total, true);
   if (wi.skip) return;
   const int32_t tile = wi.tile;
@@ -467,7 +608,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   // tile, one 4x4 group in lanes 0-15.  Each group walks its own stream of
   // entries (those meeting its still-compositing pixels), so a wave iterates
   // max over groups instead of the union of the four streams.
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wv = (int)uniform_u32(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int grp = lane >> 4;
   const bool rp = wi.quarter >= 0 && wi.rowpar;  // split work item: rows are consecutive entries
   const LanePixel lp = lane_pixel(tx, ty, wi.quarter, wv, lane, rp);
@@ -489,104 +630,148 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   // and the list indices of round R + 2 are already in flight.
   Staged cur = fetch_entry(rec, bin, start + threadIdx.x < end ? vals[start + threadIdx.x] : 0u,
                            start + threadIdx.x < end, nrec);
-  uint32_t nidx = start + kBatch + threadIdx.x < end ? vals[start + kBatch + threadIdx.x] : 0u;
-  for (uint32_t base = start; base < end; base += kBatch) {
-    if (__syncthreads_and(done)) break;  // also orders this round's LDS writes after the last round's reads
-    s_box[threadIdx.x] = cur.box;
-    s_r0[threadIdx.x] = cur.r0;
-    s_r1[threadIdx.x] = cur.r1;
-    s_r2[threadIdx.x] = make_float4(cur.r2.x, cur.r2.y, cur.r2.z, __uint_as_float(cur.idx));
-    if (DEPTH == GS_DEPTH_BLEND) s_z[threadIdx.x] = cur.z;
+  uint32_t nidx = start + kFwdBatch + threadIdx.x < end ? vals[start + kFwdBatch + threadIdx.x] : 0u;
+  const int32_t ix0 = tx * kTile + (wi.quarter > 0 ? (wi.quarter & 1) * 8 : 0);
+  const int32_t iy0 = ty * kTile + (wi.quarter > 0 ? (wi.quarter >> 1) * 8 : 0);
+  const bool split = wi.quarter >= 0;
+  for (uint32_t base = start; base < end; base += kFwdBatch) {
+    const uint32_t tid = (uint32_t)fresh((int)threadIdx.x);
+    const uint64_t am = __builtin_amdgcn_ballot_w64(!done);
+    if (lane == 0) s_round.active[wv] = am;
+    __syncthreads();  // also orders this round's LDS writes after the last round's reads
+    if (s_round.none_active()) break;
+    const uint32_t count = (end - base) < (uint32_t)kFwdBatch ? (end - base) : (uint32_t)kFwdBatch;
+    s_r0[tid] = cur.r0;
+    s_r1[tid] = cur.r1;
+    s_r2[tid] = make_float4(cur.r2.x, cur.r2.y, cur.r2.z, __uint_as_float(cur.idx));
+    if (DEPTH == GS_DEPTH_BLEND) s_z[tid] = cur.z;
     if (ACC) {
-      s_acc_w[threadIdx.x] = 0.f;
-      s_acc_m[threadIdx.x] = 0u;
+      const int zero = fresh(0);
+      s_acc_w[tid] = __hiloint2double(zero, zero);
+      s_acc_m[tid] = 0u;
     }
+    test_round(s_round, nullptr, 0u, split, fresh_uniform(ix0), fresh_uniform(iy0), cur.box, cur.r0, cur.r1, (uint32_t)tid < count, wv,
+               fresh(lane), op.log2_alpha_min);
     __syncthreads();
     {
-      const uint32_t jn = base + kBatch + threadIdx.x, jnn = jn + kBatch;
+      const uint32_t jn = base + kFwdBatch + tid, jnn = jn + kFwdBatch;
       cur = fetch_entry(rec, bin, nidx, jn < end, nrec);
       nidx = jnn < end ? vals[jnn] : 0u;
     }
-    const uint32_t count = (end - base) < (uint32_t)kBatch ? (end - base) : (uint32_t)kBatch;
-    bool wave_done = __all(done);
     if (!rp) at = kNoOffset;
-#pragma unroll 1
-    for (int c = 0; c < kBatch / kWave && !wave_done; ++c) {
-      // staged entry k against each group's still-compositing pixels
-      const int k = c * kWave + lane;
-      const bool kin = (uint32_t)k < count;
-      const int2 bx = s_box[k];
-      const float4 q0 = s_r0[k], q1 = s_r1[k];
-      const uint64_t am = __builtin_amdgcn_ballot_w64(!done);
-      const Streams st = make_streams(s_stream[wv], bx, q0, q1, kin, am, rp ? 1 : kGroups, sx0, sy0, k, lane,
-                                      op.log2_alpha_min);
+    if (am != 0) {  // some pixel of this wave still composites
+      int n4[kGroups];
+      make_streams<true>(s_round, s_stream[wv], 16, split, rp, wv, fresh(lane), n4);
       // Split work item: row r takes the r-th of the next four entries of the
       // group's stream.  The transmittance in front of each is T times the
       // product of (1 - alpha) over the rows before it; an entry is composited
       // unless its own or an earlier row's entry reaches the stop.  Each row
       // keeps partial colour, depth, count and argmax, merged at the end.
-      int left = rp ? st.n[0] : 0;
-      for (const uint16_t* sp = &s_stream[wv][0][grp]; left > 0; left -= kGroups, sp += kGroups) {
-        const bool hr = grp < left;
-        const uint32_t off = hr ? *sp : 0u;
-        const float4 r0 = lds_at(s_r0, off), r1 = lds_at(s_r1, off), q2 = lds_at(s_r2, off);
-        const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
-        const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
-        const float al = fminf(op.alpha_max, __builtin_amdgcn_exp2f(ee));
-        const bool pass = hr && !done && ee >= op.log2_alpha_min;
-        const float om = pass ? 1.f - al : 1.f;
-        const RowScan tf = rows_scan_mul(om, grp);
-        const bool stop = pass && T * tf.incl < op.t_min;
-        const uint64_t sb = __builtin_amdgcn_ballot_w64(stop);
-        bool inc = pass;
-        float Tn = T * tf.total;
-        if (sb != 0ull) {
-          // rare: some pixel stops at one of these entries; later rows of its
-          // column are dropped and its transmittance is the one in front of
-          // the stopping entry
-          const int l = fresh(lane);
-          const uint64_t col = 0x0001000100010001ull << (l & 15);
-          const bool earlier = (sb & col & ((1ull << (l & 48)) - 1ull)) != 0;
-          inc = pass && !stop && !earlier;
-          Tn = T * rows_scan_mul(inc ? om : 1.f, grp).total;
-          done = done || (sb & col) != 0;
+      // Each four is of one chunk of 64 staged entries, and a chunk's entries
+      // are those that meet the pixels compositing at its start: which entries
+      // share a product (and with it the rounding of the transmittance) does
+      // not depend on how many entries a round has.  Two fours per iteration:
+      // their records are read and their alphas and products formed side by
+      // side, then they are composited in order.
+      uint64_t met = am;  // pixels that the rest of the stream was tested against
+#pragma unroll 1
+      for (int i = 0; rp && i < n4[3];) {
+        const int row = (fresh((int)threadIdx.x) & 63) >> 4;
+        const uint64_t now = __builtin_amdgcn_ballot_w64(!done);
+        if (now == 0) break;
+        if (now != met) {  // rare: some pixel has stopped in the chunk that ended here
+          for (int from = i; from < n4[3];) {
+            const int end = from < n4[1] ? n4[1] : from < n4[2] ? n4[2] : n4[3];
+            retest_chunk(s_stream[wv][0], from, end, s_r0, s_r1, s_r2, bin, (uint32_t)now & 0xffffu, fresh_uniform(ix0), fresh_uniform(iy0),
+                         (wv & 1) * 4, (wv >> 1) * 4, fresh(lane), op.log2_alpha_min);
+            from = end;
+          }
+          met = now;
         }
-        const float wgt = inc ? al * (T * tf.excl) : 0.f;
-        c0 += wgt * q2.x;
-        c1 += wgt * q2.y;
-        c2 += wgt * q2.z;
-        if (DEPTH == GS_DEPTH_BLEND) dblend += wgt * lds_at(s_z, off >> 2);
-        const uint32_t pos = base + (off >> 4) - start;
-        const bool better = wgt > wbest;  // a row's entries arrive in order: the nearer wins ties
-        wbest = better ? wgt : wbest;
-        best = better ? __float_as_uint(q2.w) : best;
-        at = better ? pos : at;
-        lastpos = inc ? pos + 1 : lastpos;
-        cnt += inc ? 1u : 0u;
-        if (ACC && inc) {
-          atomicAdd(&s_acc_w[off >> 4], wgt);
-          atomicMax(&s_acc_m[off >> 4], __float_as_uint(wgt));
-        }
-        T = Tn;
-        if (sb != 0ull) {
-          const uint64_t dm = __builtin_amdgcn_ballot_w64(done);
-          if ((dm & 0xffffull) == 0xffffull) left = 0;
-          if (dm == ~0ull) {
-            wave_done = true;
-            break;
+        int until = n4[3];
+        const uint16_t* sp = &s_stream[wv][0][i + row];
+#pragma unroll 1
+        for (; i < until; i += 2 * kGroups, sp += 2 * kGroups) {
+          uint32_t off[2];
+          bool pass[2];
+          float4 q2[2];
+          float al[2], om[2], wg[2];
+          RowScan tf[2];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const uint32_t entry = i + u * kGroups < until ? (uint32_t)sp[u * kGroups] : kNoEntry;
+            const bool hr = entry != kNoEntry;
+            off[u] = hr ? entry : 0u;
+            const float4 r0 = lds_at(s_r0, off[u]), r1 = lds_at(s_r1, off[u]);
+            q2[u] = lds_at(s_r2, off[u]);
+            const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
+            const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
+            al[u] = fminf(op.alpha_max, __builtin_amdgcn_exp2f(ee));
+            pass[u] = hr && !done && ee >= op.log2_alpha_min;
+            om[u] = pass[u] ? 1.f - al[u] : 1.f;
+            tf[u] = rows_scan_mul(om[u], row);
+          }
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const bool stop = pass[u] && T * tf[u].incl < op.t_min;
+            const uint64_t sb = __builtin_amdgcn_ballot_w64(stop);
+            bool inc = pass[u];
+            float Tn = T * tf[u].total;
+            if (sb != 0ull) {
+              // rare: some pixel stops at one of these entries; later rows of its
+              // column are dropped and its transmittance is the one in front of
+              // the stopping entry
+              const int l = fresh(lane);
+              const uint64_t col = 0x0001000100010001ull << (l & 15);
+              const bool earlier = (sb & col & ((1ull << (l & 48)) - 1ull)) != 0;
+              inc = pass[u] && !stop && !earlier;
+              Tn = T * rows_scan_mul(inc ? om[u] : 1.f, row).total;
+              done = done || (sb & col) != 0;
+              // the walk leaves off at the end of this chunk, which may be
+              // between the two fours (row 0 of a four always has an entry)
+              const uint32_t chunk = uniform_u32(off[u]) / (16u * kWave);
+              until = chunk == 0 ? n4[0] : chunk == 1 ? n4[1] : chunk == 2 ? n4[2] : n4[3];
+              if (u == 0) {
+                pass[1] = pass[1] && !done && i + kGroups < until;
+                om[1] = pass[1] ? om[1] : 1.f;
+                tf[1] = rows_scan_mul(om[1], row);
+              }
+            }
+            const float wgt = inc ? al[u] * (T * tf[u].excl) : 0.f;
+            c0 += wgt * q2[u].x;
+            c1 += wgt * q2[u].y;
+            c2 += wgt * q2[u].z;
+            if (DEPTH == GS_DEPTH_BLEND) dblend += wgt * lds_at(s_z, off[u] >> 2);
+            const uint32_t pos = base + (off[u] >> 4) - start;
+            const bool better = wgt > wbest;  // a row's entries arrive in order: the nearer wins ties
+            wbest = better ? wgt : wbest;
+            best = better ? __float_as_uint(q2[u].w) : best;
+            at = better ? pos : at;
+            lastpos = inc ? pos + 1 : lastpos;
+            cnt += inc ? 1u : 0u;
+            wg[u] = wgt;
+            T = Tn;
+          }
+          if (ACC) {
+            const SumMax r = row_sum_max2(wg[0], wg[1]);
+            if ((lane & 7) == 0 && r.max > 0.f) {
+              const uint32_t k = ((lane & 8) ? off[1] : off[0]) >> 4;
+              atomicAdd(&s_acc_w[k], (double)r.sum);
+              atomicMax(&s_acc_m[k], __float_as_uint(r.max));
+            }
           }
         }
+        i = until;
       }
-      if (rp) continue;
       // kFwdUnroll entries of the group's stream per iteration: their records
       // are read and their alphas evaluated side by side, then they are
       // composited in order (each sees the previous one's transmittance and
       // stop), so the result is that of one-by-one compositing with a fraction
       // of the loop latency.  The offsets of the next iteration are read ahead.
-      int mine = grp == 0 ? st.n[0] : grp == 1 ? st.n[1] : grp == 2 ? st.n[2] : st.n[3];
-      const int n01 = st.n[0] > st.n[1] ? st.n[0] : st.n[1], n23 = st.n[2] > st.n[3] ? st.n[2] : st.n[3];
-      const int longest = n01 > n23 ? n01 : n23;
-      const uint32_t* sp = reinterpret_cast<const uint32_t*>(&s_stream[wv][grp][0]);
+      const int group = (fresh((int)threadIdx.x) & 63) >> 4;
+      int mine = group == 0 ? n4[0] : group == 1 ? n4[1] : group == 2 ? n4[2] : n4[3];
+      const int longest = rp ? 0 : max4(n4);
+      const uint32_t* sp = reinterpret_cast<const uint32_t*>(&s_stream[wv][group][0]);
       uint32_t pair = *sp;
       for (int i = 0; i < longest; i += kFwdUnroll) {
         uint32_t off[kFwdUnroll];
@@ -596,10 +781,10 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
           has[u] = i + u < mine;
           off[u] = (pair >> (16 * u)) & 0xffffu;
         }
-        sp += i + kFwdUnroll < kWave ? 1 : 0;
+        sp += i + kFwdUnroll < kFwdBatch ? 1 : 0;
         pair = *sp;
         float4 q2[kFwdUnroll];
-        float al[kFwdUnroll], ee[kFwdUnroll];
+        float al[kFwdUnroll], ee[kFwdUnroll], wg[kFwdUnroll];
 #pragma unroll
         for (int u = 0; u < kFwdUnroll; ++u) {
           const float4 r0 = lds_at(s_r0, off[u]), r1 = lds_at(s_r1, off[u]);
@@ -629,31 +814,31 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
           best = better ? __float_as_uint(q2[u].w) : best;
           at = inc ? off[u] : at;
           cnt += inc ? 1u : 0u;
-          if (ACC && inc) {
-            // each including lane adds its weight to the entry's LDS slot (no
-            // reply awaited, so nothing on this wave's dependency chain);
-            // weights are >= 0, so the max runs on bit patterns
-            atomicAdd(&s_acc_w[off[u] >> 4], wgt);
-            atomicMax(&s_acc_m[off[u] >> 4], __float_as_uint(wgt));
+          wg[u] = wgt;
+        }
+        if (ACC) {
+          const SumMax r = row_sum_max2(wg[0], wg[1]);
+          if ((lane & 7) == 0 && r.max > 0.f) {
+            const uint32_t k = ((lane & 8) ? off[1] : off[0]) >> 4;
+            atomicAdd(&s_acc_w[k], (double)r.sum);
+            atomicMax(&s_acc_m[k], __float_as_uint(r.max));  // weights are >= 0: bit patterns have their order
           }
         }
         // a group whose pixels have all stopped drops the rest of its stream
         const uint64_t dm = __builtin_amdgcn_ballot_w64(done);
-        if (((dm >> (16 * grp)) & 0xffffull) == 0xffffull) mine = 0;
-        if (dm == ~0ull) {
-          wave_done = true;
-          break;
-        }
+        if (((dm >> (16 * group)) & 0xffffull) == 0xffffull) mine = 0;
+        if (dm == ~0ull) break;
       }
     }
     if (!rp && at != kNoOffset) lastpos = base - start + (at >> 4) + 1;
     if (ACC) {
       __syncthreads();
-      if ((uint32_t)threadIdx.x < count && s_acc_m[threadIdx.x] != 0u) {
-        const uint32_t r = __float_as_uint(s_r2[threadIdx.x].w);
+      const uint32_t ft = (uint32_t)fresh((int)threadIdx.x);
+      if (ft < count && s_acc_m[ft] != 0u) {
+        const uint32_t r = __float_as_uint(s_r2[ft].w);
         const int64_t ai = per_view ? (int64_t)r : (int64_t)r - vbase;
-        if (o.imp) atomicAdd(o.imp + ai, s_acc_w[threadIdx.x]);
-        if (o.wmax) atomicMax(reinterpret_cast<unsigned int*>(o.wmax) + ai, s_acc_m[threadIdx.x]);
+        if (o.imp) atomicAdd(o.imp + ai, (float)s_acc_w[ft]);
+        if (o.wmax) atomicMax(reinterpret_cast<unsigned int*>(o.wmax) + ai, s_acc_m[ft]);
       }
     }
   }
@@ -677,7 +862,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
       best = take_b ? b.b : b.a;
       at = take_b ? q.b : q.a;
     }
-    if (grp != 0) return;  // row 0 writes the pixel
+    if (lane >= 16) return;  // row 0 writes the pixel
   }
   const LanePixel le = lane_pixel(tx, ty, wi.quarter, wv, fresh(lane), rp);
   const int32_t px = le.px, py = le.py;
@@ -720,7 +905,6 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
 // so the walk needs no separate flag.  A corrupt index (outside this view's
 // records) is replaced by an inactive entry with an empty box.
 struct StagedB {
-  uint32_t idx;
   int2 box;
   float4 r0, r1, r2;
 };
@@ -732,7 +916,6 @@ __device__ __forceinline__ StagedB fetch_entry_bwd(const float* __restrict__ rec
   const bool valid = in_list && (int64_t)r < nrec && (int64_t)r >= vbase;
   r = valid ? r : (uint32_t)vbase;
   const bool act = valid && (!MASKED || active[(int64_t)r - vbase] != 0);
-  e.idx = r;
   e.box = valid ? *reinterpret_cast<const int2*>(bin + 4 * (int64_t)r) : make_int2(0xffff, 0xffff);
   const float4* R4 = reinterpret_cast<const float4*>(rec + (int64_t)r * kRecFloats);
   e.r0 = R4[0];
@@ -810,9 +993,14 @@ __device__ __forceinline__ float g2d_component(int c, float x, float y, float A,
 // gradient once per round, or (deterministic reduction) into the entry's slot
 // for this group (list position j, group g16 of the tile's sixteen 4x4
 // groups), marked in the entry's mask.  A slot is written at most once: each
-// group walks an entry at most once.
-template <bool DET>
-__device__ __forceinline__ void emit_partial(float* s_acc, float* __restrict__ part, uint32_t* __restrict__ pmask,
+// group walks an entry at most once.  LDS adds floats one lane at a time:
+// ds_add_f32 occupies the CU's LDS for 2.9 cycles per active lane (104 for these
+// 36 lanes, more than the iteration's vector instructions take), ds_add_f64 for
+// 8 cycles in all.  So the accumulators are double where every Gaussian is
+// active, and float under an active mask, where few lanes add and the longer
+// rounds are worth more.
+template <bool DET, typename Acc>
+__device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ part, uint32_t* __restrict__ pmask,
                                              uint32_t k, uint32_t base, int g16, int slot, uint64_t cm, int grp,
                                              float val) {
   if (slot < 0 || ((cm >> (16 * grp)) & 0xffffull) == 0) return;
@@ -821,7 +1009,7 @@ __device__ __forceinline__ void emit_partial(float* s_acc, float* __restrict__ p
     part[((int64_t)j * 16 + g16) * kG2d + slot] = val;
     if (slot == 8) atomicOr(pmask + j, 1u << g16);
   } else {
-    atomicAdd(s_acc + (uint32_t)__umul24(k, (uint32_t)kG2d) + slot, val);
+    atomicAdd(s_acc + (uint32_t)__umul24(k, (uint32_t)kG2d) + slot, (Acc)val);
   }
 }
 
@@ -838,8 +1026,10 @@ __device__ __forceinline__ void emit_partial(float* s_acc, float* __restrict__ p
 // One global atomic per (entry, workgroup) and component instead of one per
 // (entry, group): float atomics are carried out at the memory side (at most
 // ~17 G requests/s), which bounded the kernel where most entries are active
-// (1M Gaussians, 16 views, 17.3M pixels, all active: 169M -> 31M requests,
-// with the streams below and the scalar suffix 9.76 -> 6.42 ms).
+// (1M Gaussians, 16 views, 17.3M pixels, all active: 169M -> 31M requests).
+// Now bound by the vector instructions of the walk.  Measured there: with
+// those sums, list streams and the scalar suffix 9.76 -> 6.42 ms; with the
+// tests in the staging thread 5.80 ms; with double accumulators 4.34 ms.
 template <bool MASKED, bool DET>
 __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
                                                        const uint32_t* __restrict__ vals,
@@ -851,19 +1041,18 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
                                                        const uint8_t* __restrict__ active, float* __restrict__ g2d,
                                                        float* __restrict__ part, uint32_t* __restrict__ pmask,
                                                        KOpts op, ViewSet vs) {
+  constexpr int kBatch = kBwdBatch<MASKED, DET>;
+  using Acc = std::conditional_t<MASKED, float, double>;
   __shared__ float4 s_r0[kBatch], s_r1[kBatch], s_r2[kBatch];
-  __shared__ int2 s_box[kBatch];
-  __shared__ uint32_t s_idx[DET ? 1 : kBatch];
+  __shared__ RoundLds<kBatch> s_round;
   // the staged entries' sums over the workgroup; all zero at the start of a round
-  __shared__ float s_acc[DET ? 1 : kBatch * kG2d];
-  constexpr int kChunks = kBatch / kWave;
-  __shared__ uint64_t s_walk[kChunks][kBlock / kWave];  // entries of a chunk that a wave may have walked
-  __shared__ uint8_t s_list[kChunks][kWave];
-  __shared__ uint16_t s_stream[kBlock / kWave][kGroups][kWave];
-  for (int q = threadIdx.x; q < kBlock / kWave * kGroups * kWave; q += kBlock) (&s_stream[0][0][0])[q] = 0;
+  __shared__ Acc s_acc[DET ? 1 : kBatch * kG2d];
+  __shared__ uint8_t s_stream[kWaves][kGroups][kBatch];
+  __shared__ uint32_t s_last[kWaves * kGroups];  // largest `last` of each group
+  for (int q = threadIdx.x; q < kWaves * kGroups * kBatch / 4; q += kBlock)
+    reinterpret_cast<uint32_t*>(&s_stream[0][0][0])[q] = 0;
   if (!DET)
-    for (int q = threadIdx.x; q < kBatch * kG2d; q += kBlock) s_acc[q] = 0.f;
-  __shared__ uint32_t s_jmax[kBlock / kWave];
+    for (int q = threadIdx.x; q < kBatch * kG2d; q += kBlock) s_acc[q] = Acc(0);
   const WorkItem wi = work_item(order, ranges, nsplit, vs.tiles_total, false);
   if (wi.skip) return;
   const int32_t tile = wi.tile;
@@ -871,7 +1060,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   const KView& cam = vs.v[v];
   const int32_t lt = tile - cam.tile_base;
   const int32_t tx = lt % cam.tiles_x, ty = lt / cam.tiles_x;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wv = (int)uniform_u32(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int grp = lane >> 4;
   const bool rp = wi.quarter >= 0;  // split work item: rows are consecutive entries
   const LanePixel lp = lane_pixel(tx, ty, wi.quarter, wv, lane, rp);
@@ -899,52 +1088,58 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   lst = lst < end - start ? lst : end - start;  // `last` never exceeds the tile's list
   float S = T * (g0 * op.bg[0] + g1 * op.bg[1] + g2 * op.bg[2]);  // dL/dcolour . colour composited behind
   const int slot = sum_slot(lane);  // the sum this lane emits after row_sum9, or -1
-  const uint32_t wjmax = uniform_u32(wave_max_u32(lst));
-  if (lane == 0) s_jmax[wv] = wjmax;
+  {
+    uint32_t m = lst;  // over the 16 lanes of a group; split rows hold the same pixels
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const uint32_t y = __shfl_xor(m, o, kWave);
+      m = y > m ? y : m;
+    }
+    if ((lane & 15) == 0) s_last[wv * kGroups + grp] = m;
+  }
   __syncthreads();
   uint32_t bjmax = 0;
 #pragma unroll
-  for (int k = 0; k < kBlock / kWave; ++k) bjmax = s_jmax[k] > bjmax ? s_jmax[k] : bjmax;
+  for (int k = 0; k < kWaves * kGroups; ++k) bjmax = s_last[k] > bjmax ? s_last[k] : bjmax;
+  bjmax = uniform_u32(bjmax);
+  const int32_t ix0 = tx * kTile + (rp ? (wi.quarter & 1) * 8 : 0), iy0 = ty * kTile + (rp ? (wi.quarter >> 1) * 8 : 0);
   // Rounds cover [base, top) downwards from start + bjmax.  Staging pipeline:
   // the records of the next round and the list indices of the one after are
   // in flight while a round is processed.
   auto round_base = [&](uint32_t top) { return top - start > (uint32_t)kBatch ? top - kBatch : start; };
   uint32_t top = start + bjmax;
   uint32_t base = round_base(top);
-  StagedB cur = fetch_entry_bwd<MASKED>(rec, bin, active, base + threadIdx.x < top ? vals[base + threadIdx.x] : 0u,
-                                        base + threadIdx.x < top, nrec, vbase);
+  const uint32_t mine_at = threadIdx.x;
+  const bool stager = mine_at < (uint32_t)kBatch;
+  StagedB cur = fetch_entry_bwd<MASKED>(rec, bin, active, stager && base + mine_at < top ? vals[base + mine_at] : 0u,
+                                        stager && base + mine_at < top, nrec, vbase);
   uint32_t nbase = round_base(base), ntop = base;
-  uint32_t nidx = nbase + threadIdx.x < ntop ? vals[nbase + threadIdx.x] : 0u;
+  uint32_t nidx = stager && nbase + mine_at < ntop ? vals[nbase + mine_at] : 0u;
   while (top > start) {
     const uint32_t count = top - base;
+    // pixels whose last entry lies above the round's first
+    const uint64_t am = __builtin_amdgcn_ballot_w64(lst > base - start);
+    if (lane == 0) s_round.active[wv] = am;
     __syncthreads();  // the previous round's entries are consumed
-    if (!DET) {
-      s_idx[threadIdx.x] = cur.idx;
-      if (threadIdx.x < kChunks * (kBlock / kWave)) (&s_walk[0][0])[threadIdx.x] = 0ull;
+    if (stager) {
+      s_r0[mine_at] = cur.r0;
+      s_r1[mine_at] = cur.r1;
+      s_r2[mine_at] = cur.r2;
     }
-    s_box[threadIdx.x] = cur.box;
-    s_r0[threadIdx.x] = cur.r0;
-    s_r1[threadIdx.x] = cur.r1;
-    s_r2[threadIdx.x] = cur.r2;
+    uint64_t walked = test_round(s_round, s_last, base + mine_at - start, rp, ix0, iy0, cur.box, cur.r0, cur.r1,
+                                 stager && mine_at < count, wv, fresh(lane), op.log2_alpha_min);
+    if (MASKED) walked &= __builtin_amdgcn_ballot_w64(cur.r2.w > 0.f);
     __syncthreads();
     {
       // next round [nbase, ntop) and the one after it
-      cur = fetch_entry_bwd<MASKED>(rec, bin, active, nidx, ntop > start && nbase + threadIdx.x < ntop, nrec, vbase);
+      cur = fetch_entry_bwd<MASKED>(rec, bin, active, nidx, stager && ntop > start && nbase + mine_at < ntop, nrec,
+                                    vbase);
       const uint32_t nnbase = round_base(nbase);
-      nidx = (nbase > start && nnbase + threadIdx.x < nbase) ? vals[nnbase + threadIdx.x] : 0u;
+      nidx = (stager && nbase > start && nnbase + mine_at < nbase) ? vals[nnbase + mine_at] : 0u;
     }
-#pragma unroll 1
-    for (int c = kBatch / kWave - 1; c >= 0; --c) {
-      const int k = c * kWave + lane;
-      // lanes that still have work in this chunk: their last entry lies above its first
-      const uint64_t am = __builtin_amdgcn_ballot_w64(lst > base + (uint32_t)(c * kWave) - start);
-      if (am == 0) continue;
-      const bool kin = (uint32_t)k < count && base + (uint32_t)k < start + wjmax;
-      const int2 bx = s_box[k];
-      const float4 q0 = s_r0[k], q1 = s_r1[k];
-      const Streams st = make_streams(s_stream[wv], bx, q0, q1, kin, am, rp ? 1 : kGroups, sx0, sy0, k, lane,
-                                      op.log2_alpha_min);
-      if (!DET && lane == 0) s_walk[c][wv] = st.any;
+    if (am != 0) {
+      int n4[kGroups];
+      make_streams<false>(s_round, s_stream[wv], 1, rp, false, wv, fresh(lane), n4);
       // round-relative offset from which on the pixel composited nothing
       const uint32_t lim = lst > base - start ? (lst - (base - start)) * 16u : 0u;
       // Split work item: row r takes the r-th latest of the next four entries
@@ -952,10 +1147,10 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       // product of 1 / (1 - alpha) over the rows up to it, its suffix colour
       // the sum of the weighted colours of the rows before it; the nine
       // partials of each row's entry are then summed over the row as usual.
-      int left = rp ? st.n[0] : 0;
-      for (const uint16_t* sp = &s_stream[wv][0][0] + left - 1 - grp; left > 0; left -= kGroups, sp -= kGroups) {
+      int left = rp ? n4[0] : 0;
+      for (const uint8_t* sp = &s_stream[wv][0][0] + left - 1 - grp; left > 0; left -= kGroups, sp -= kGroups) {
         const bool hr = grp < left;
-        const uint32_t off = hr ? *sp : 0u;
+        const uint32_t off = hr ? (uint32_t)*sp * 16u : 0u;
         const bool val = hr && off < lim;
         const float4 r0 = lds_at(s_r0, off), r1 = lds_at(s_r1, off), c4 = lds_at(s_r2, off);
         const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
@@ -988,20 +1183,17 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const uint64_t cm = __builtin_amdgcn_ballot_w64(act);
         if (cm != 0) emit_partial<DET>(s_acc, part, pmask, off >> 4, base, g16, slot, cm, grp, row_sum9(pv, lane));
       }
-      if (rp) continue;
       // One entry of the group's stream per iteration, latest first; the
       // transmittance is restored through them in reverse order.
-      const int mine = grp == 0 ? st.n[0] : grp == 1 ? st.n[1] : grp == 2 ? st.n[2] : st.n[3];
-      const int n01 = st.n[0] > st.n[1] ? st.n[0] : st.n[1], n23 = st.n[2] > st.n[3] ? st.n[2] : st.n[3];
-      const int longest = n01 > n23 ? n01 : n23;
-      const uint16_t* const first = &s_stream[wv][grp][0];
-      const uint16_t* sp = first + (mine > 0 ? mine - 1 : 0);
-      uint32_t off = *sp;
+      const int mine = grp == 0 ? n4[0] : grp == 1 ? n4[1] : grp == 2 ? n4[2] : n4[3];
+      const int longest = rp ? 0 : max4(n4);
+      const uint8_t* sp = &s_stream[wv][grp][0] + (mine > 0 ? mine - 1 : 0);
+      uint32_t off = (uint32_t)*sp * 16u;
       for (int i = 0; i < longest; ++i) {
         const uint32_t at = off;
         const bool val = i < mine && at < lim;
         sp -= i + 1 < mine ? 1 : 0;
-        off = *sp;
+        off = (uint32_t)*sp * 16u;
         const float4 r0 = lds_at(s_r0, at), r1 = lds_at(s_r1, at), c4 = lds_at(s_r2, at);
         const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
         const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
@@ -1038,29 +1230,30 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       }
     }
     if (!DET) {
-      // Wave w adds chunk w's walked active entries to their records, seven
-      // entries of nine consecutive components at a time, so an entry's adds
-      // leave in one or two requests, and clears what it has read.
+      // Wave w adds the walked active entries of chunk w, which it tested, to
+      // their records: seven entries of nine consecutive components at a time,
+      // so an entry's adds leave in one or two requests.  It clears what it
+      // has read.
       __syncthreads();
       const int fl = fresh(lane);
       const int fe = fl / kG2d, fc = fl - fe * kG2d;
-      const int kf = wv * kWave + fl;
-      uint64_t m = __ballot(!MASKED || s_r2[kf].w > 0.f);
-      uint64_t walked = 0;
-#pragma unroll
-      for (int q = 0; q < kBlock / kWave; ++q) walked |= s_walk[wv][q];
-      m &= uniform_u64(walked);
-      const int cnt = (int)__popcll(m);
-      if ((m >> fl) & 1ull) s_list[wv][__popcll(m & ((1ull << fl) - 1ull))] = (uint8_t)fl;
+      const int cnt = (int)__popcll(walked);
+      uint8_t* list = &s_stream[wv][0][0];  // this wave's streams are walked
+      if (__builtin_amdgcn_inverse_ballot_w64(walked))
+        list[__builtin_amdgcn_mbcnt_hi((uint32_t)(walked >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)walked, 0u))] =
+            (uint8_t)(wv * kWave + fl);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
       for (int e = fe < kWave / kG2d ? fe : kWave; e < cnt; e += kWave / kG2d) {
-        const int k = wv * kWave + (int)s_list[wv][e];
-        float* ap = s_acc + k * kG2d;
-        const float x = ap[fc], y = ap[fc ^ (fc < 2 ? 1 : 0)];
-        ap[fc] = 0.f;
+        const uint32_t k = list[e];
+        const uint32_t r = vals[base + k];  // a walked entry's index is valid
+        Acc* ap = s_acc + k * kG2d;
+        const float x = (float)ap[fc], y = (float)ap[fc ^ (fc < 2 ? 1 : 0)];
+        ap[fc] = Acc(0);
         const float4 r1 = s_r1[k];
         const float val = g2d_component(fc, x, y, r1.x, r1.y, r1.z, fabsf(s_r2[k].w));
-        if (val != 0.f) atomicAdd(g2d + (int64_t)s_idx[k] * kG2d + fc, val);
+        if (val != 0.f) atomicAdd(g2d + (int64_t)r * kG2d + fc, val);
       }
     }
     top = base;
