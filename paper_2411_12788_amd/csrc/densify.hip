@@ -9,10 +9,11 @@
 //
 // The threshold never sorts: four 8-bit radix-select passes narrow a 32-bit
 // order-preserving key down to the element(s) the threshold needs.  Each pass
-// reads the values once (coalesced, grid-stride), histograms the current digit
-// in LDS and flushes non-empty bins with one global atomic each; a one-block
-// step kernel per problem then chooses the bin.  Nothing is sorted or
-// compacted, so the cost is ~4-5 streaming reads of the input.
+// is one kernel: it reads the values once, histograms the current digit in LDS
+// and flushes non-empty bins with one global atomic each; the last workgroup of
+// a problem then chooses the bin, and after the fourth pass the threshold.
+// Nothing is sorted or compacted, so the cost is 5 streaming reads of the
+// input and the launches.
 #include <cmath>
 
 #include "common.hpp"
@@ -49,8 +50,8 @@ struct SelState {
   double target;        // mass mode: keep * S
   double frac;          // value mode: interpolation weight
   uint32_t min_above;   // mass mode: smallest key above the final group
-  int32_t need_above;   // mass mode: the threshold is that key's value
-  int32_t pad[2];
+  uint32_t done;        // workgroups of the running pass that have flushed
+  int32_t all_ties;     // rank mode: every value equal to the k-th smallest is among the k
 };
 
 struct SelHist {
@@ -75,17 +76,40 @@ struct Source {
   const uint32_t* area;  // NULL: select values > 0
   const float* expo;     // NULL: the key is the value itself
   int64_t n;
-  __device__ __forceinline__ bool take(int p, int64_t i, float& v) const {
+  // Elements i, i + STEP, ..: their keys' values, and in bit u of the result
+  // whether element i + u STEP is selected.  All loads are issued before the
+  // first value is used.
+  template <int U, int STEP = kBlock>
+  __device__ __forceinline__ uint32_t take_many(int p, int64_t i, float (&v)[U]) const {
     const int64_t j = (int64_t)p * n + i;
-    v = values[j];
-    bool s = area ? (area[j] > 0u) : (v > 0.0f);
-    if (expo) {
-      s = s && v > 0.0f;
-      v = expo[j] / v;  // IEEE-rounded float division
+    uint32_t a[U], m = 0u;
+    float e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i + u * STEP < n ? values[j + u * STEP] : 0.0f;
+    if (area) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) a[u] = i + u * STEP < n ? area[j + u * STEP] : 0u;
     }
-    return s;
+    if (expo) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) e[u] = i + u * STEP < n ? expo[j + u * STEP] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      bool s = area ? a[u] > 0u : v[u] > 0.0f;
+      if (expo) {
+        s = s && v[u] > 0.0f;
+        v[u] = e[u] / v[u];  // IEEE-rounded float division
+      }
+      m |= s ? 1u << u : 0u;
+    }
+    return m;
   }
 };
+constexpr int kSelBatch = 8;             // elements of a thread whose loads are in flight together
+constexpr int kSelBlock = 1024;          // threads per workgroup of a pass
+constexpr int kSelStep = kSelBlock * kSelBatch;  // its elements per step
+constexpr int kApplyChunk = kBlock * 16;   // elements of a workgroup of the mask kernel per step
 
 // Selection modes: the two threshold readings, and the k-th smallest key.
 enum { kModeValue = 0, kModeMass = 1, kModeRank = 2 };
@@ -93,49 +117,6 @@ enum { kModeValue = 0, kModeMass = 1, kModeRank = 2 };
 __global__ __launch_bounds__(kBlock) void k_sel_init(uint8_t* ws) {
   uint32_t* w = (uint32_t*)(ws + (size_t)blockIdx.x * kSelStride);
   for (int i = threadIdx.x; i < (int)(kSelStride / 4); i += kBlock) w[i] = 0u;
-}
-
-// One radix pass: histogram digit `pass` of the keys that match each target's
-// prefix.  Value mode histograms two targets (after pass 0); mass mode one,
-// with the per-bin sum of the values.
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_sel_hist(Source src, uint8_t* ws, int pass) {
-  constexpr bool MASS = MODE == kModeMass;
-  __shared__ uint32_t s_cnt[2][kSelBins];
-  __shared__ double s_sum[MASS ? kSelBins : 1];
-  const int p = blockIdx.y;
-  const SelState* st = sel_state(ws, p);
-  for (int b = threadIdx.x; b < kSelBins; b += kBlock) {
-    s_cnt[0][b] = 0u;
-    s_cnt[1][b] = 0u;
-    if (MASS) s_sum[b] = 0.0;
-  }
-  const int shift = 24 - 8 * pass;
-  const uint32_t hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (32 - 8 * pass));
-  const uint32_t pre0 = st->prefix[0], pre1 = st->prefix[1];
-  const bool two = MODE == kModeValue && pass > 0;
-  __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < src.n; i += stride) {
-    float v;
-    if (!src.take(p, i, v)) continue;
-    const uint32_t k = order_key(v);
-    const uint32_t d = (k >> shift) & 0xFFu;
-    if (((k ^ pre0) & hi_mask) == 0u) {
-      atomicAdd(&s_cnt[0][d], 1u);
-      if (MASS) atomicAdd(&s_sum[d], (double)v);
-    }
-    if (two && ((k ^ pre1) & hi_mask) == 0u) atomicAdd(&s_cnt[1][d], 1u);
-  }
-  __syncthreads();
-  SelHist* h = sel_hist(ws, p);
-  for (int b = threadIdx.x; b < kSelBins; b += kBlock) {
-    if (s_cnt[0][b]) {
-      atomicAdd(&h->cnt[0][b], s_cnt[0][b]);
-      if (MASS) atomicAdd(&h->sum[b], s_sum[b]);
-    }
-    if (two && s_cnt[1][b]) atomicAdd(&h->cnt[1][b], s_cnt[1][b]);
-  }
 }
 
 __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t x) {
@@ -191,28 +172,15 @@ __device__ __forceinline__ void rank_walk(const uint32_t* c, int64_t r, int& bin
   below = (int64_t)__shfl(cand_below, bin >> 2, kWave);
 }
 
-// Choose the bin of each target and clear the histograms for the next pass.
-// One block per problem; the histogram is staged in LDS and one wave walks it.
+// Choose the bin of each target from a pass's histograms (one wave); after the
+// last pass, the threshold.
 template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_sel_step(uint8_t* ws, int pass, double q_or_keep) {
+__device__ __forceinline__ void sel_step(const SelState& now, SelState* st, const uint32_t (*s_cnt)[kSelBins], const double* s_sum,
+                                         uint32_t min_above, int pass, double q_or_keep, double* tau) {
   constexpr bool MASS = MODE == kModeMass;
-  __shared__ uint32_t s_cnt[2][kSelBins];
-  __shared__ double s_sum[MASS ? kSelBins : 1];
-  const int p = blockIdx.x;
-  SelState* st = sel_state(ws, p);
-  SelHist* h = sel_hist(ws, p);
-  for (int b = threadIdx.x; b < kSelBins; b += kBlock) {
-    s_cnt[0][b] = h->cnt[0][b];
-    s_cnt[1][b] = h->cnt[1][b];
-    if (MASS) s_sum[b] = h->sum[b];
-  }
-  __syncthreads();
-  uint32_t* w = (uint32_t*)h;
-  for (int i = threadIdx.x; i < (int)(sizeof(SelHist) / 4); i += kBlock) w[i] = 0u;
-  if (threadIdx.x >= kWave) return;
   const int l = (int)lane_id();
   const int shift = 24 - 8 * pass;
-  int64_t m = st->m;
+  int64_t m = now.m;
   if (pass == 0) {
     uint64_t c = 0;
     for (int j = 0; j < 4; ++j) c += s_cnt[0][4 * l + j];
@@ -232,9 +200,9 @@ __global__ __launch_bounds__(kBlock) void k_sel_step(uint8_t* ws, int pass, doub
     const double sincl = wave_incl_scan(ls);
     double soff = sincl - ls;
     uint64_t coff = wave_incl_scan(lc) - lc;
-    double target = st->target;
+    double target = now.target;
     if (pass == 0) target = q_or_keep * __shfl(sincl, kWave - 1, kWave);
-    const double before = st->mass_before;
+    const double before = now.mass_before;
     int first = kSelBins, last = -1;
     double f_sum = 0.0, l_sum = 0.0;
     uint64_t f_cnt = 0, l_cnt = 0;
@@ -264,19 +232,46 @@ __global__ __launch_bounds__(kBlock) void k_sel_step(uint8_t* ws, int pass, doub
       above_sum = __shfl(l_sum, pos >> 2, kWave);
       above_cnt = __shfl(l_cnt, pos >> 2, kWave);
     }
+    // the smallest selected key above the chosen bin: of its group if there is one
+    int next = -1;
+    for (int j = 0; j < 4; ++j)
+      if (cj[j] != 0 && 4 * l + j < pos) next = 4 * l + j;
+    next = wave_max_i(next);
     if (l == 0) {
       if (pass == 0) {
         st->m = m;
         st->target = target;
       }
+      const double mass_before = before + above_sum;
+      const int64_t before_cnt = now.before_cnt + (int64_t)above_cnt;
+      const uint32_t group = now.prefix[0];
+      const uint32_t prefix = m > 0 ? group | (uint32_t)(kSelBins - 1 - pos) << shift : group;
       if (m > 0) {
-        st->mass_before = before + above_sum;
-        st->before_cnt += (int64_t)above_cnt;
-        st->prefix[0] |= (uint32_t)(kSelBins - 1 - pos) << shift;
+        st->mass_before = mass_before;
+        st->before_cnt = before_cnt;
+        st->prefix[0] = prefix;
+      }
+      if (pass == kSelPasses - 1) {
+        // The final group holds equal values x.  The first prefix sum reaching
+        // the target lies in the group; if it is the group's first element and
+        // the previous prefix sum is at least as close, the threshold is the
+        // smallest selected value above x.
+        const double x = (double)key_value(prefix);
+        const double need = target - mass_before;
+        // the first j >= 1 with mass_before + j x >= target
+        const bool first_of_group = !(x > 0.0) || need <= x;
+        bool need_above = false;
+        if (first_of_group && before_cnt > 0) {
+          const double d_hi = mass_before + x - target;
+          const double d_lo = target - mass_before;
+          need_above = d_lo <= d_hi;
+        }
+        const uint32_t above = next >= 0 ? group | (uint32_t)(kSelBins - 1 - next) : min_above;
+        *tau = m == 0 ? __builtin_nan("") : (double)key_value(need_above ? above : prefix);
       }
     }
   } else {
-    int64_t rank[2] = {st->rank[0], st->rank[1]};
+    int64_t rank[2] = {now.rank[0], now.rank[1]};
     double frac = 0.0;
     if (pass == 0 && m > 0 && MODE == kModeRank) {
       // the k-th smallest key (k = q_or_keep, at most m)
@@ -293,6 +288,7 @@ __global__ __launch_bounds__(kBlock) void k_sel_step(uint8_t* ws, int pass, doub
       rank[1] = ilo + 1 < m ? ilo + 1 : ilo;
     }
     int bins[2] = {0, 0};
+    if (pass > 0) frac = now.frac;
     constexpr int targets = MODE == kModeValue ? 2 : 1;
     for (int t = 0; t < targets; ++t) {
       int64_t below = 0;
@@ -307,91 +303,175 @@ __global__ __launch_bounds__(kBlock) void k_sel_step(uint8_t* ws, int pass, doub
       if (m > 0) {
         for (int t = 0; t < targets; ++t) {
           st->rank[t] = rank[t];
-          st->prefix[t] |= (uint32_t)bins[t] << shift;
+          st->prefix[t] = now.prefix[t] | (uint32_t)bins[t] << shift;
         }
+      }
+      if (pass == kSelPasses - 1) {
+        double t;
+        if (m == 0 || (MODE == kModeRank && rank[0] < 0)) {
+          t = __builtin_nan("");
+        } else if (MODE == kModeRank) {
+          t = (double)key_value(now.prefix[0] | (uint32_t)bins[0]);
+          // (0 and -0 are equal values with different keys)
+          st->all_ties = t != 0.0 && rank[0] + 1 == (int64_t)s_cnt[0][bins[0]];
+        } else {
+          // a + frac (b - a)
+          const double a = (double)key_value(now.prefix[0] | (uint32_t)bins[0]);
+          const double b = (double)key_value(now.prefix[1] | (uint32_t)bins[1]);
+          const double prod = frac * (b - a);
+          t = a + prod;
+        }
+        *tau = t;
       }
     }
   }
 }
 
-// Mass mode, after the last pass: the final group holds equal values x.  The
-// first prefix sum reaching the target lies in the group; if it is the group's
-// first element and the previous prefix sum is at least as close, the
-// threshold is the smallest selected value above x.
-__global__ __launch_bounds__(kBlock) void k_sel_group(uint8_t* ws) {
-  SelState* st = sel_state(ws, blockIdx.x);
-  if (threadIdx.x != 0 || st->m == 0) return;
-  const double x = (double)key_value(st->prefix[0]);
-  const double need = st->target - st->mass_before;
-  // the first j >= 1 with mass_before + j x >= target
-  const bool first = !(x > 0.0) || need <= x;
-  st->need_above = 0;
-  if (first && st->before_cnt > 0) {
-    const double d_hi = st->mass_before + x - st->target;
-    const double d_lo = st->target - st->mass_before;
-    if (d_lo <= d_hi) st->need_above = 1;
-  }
-  st->min_above = 0xFFFFFFFFu;
-}
-
-__global__ __launch_bounds__(kBlock) void k_sel_min_above(Source src, uint8_t* ws) {
+// One radix pass: histogram digit `pass` of the keys that match each target's
+// prefix, then (the problem's last workgroup to finish) the choice of its bin.
+// Value mode histograms two targets (after pass 0); mass mode one, with the
+// per-bin sum of the values.
+//
+// At 1M values a pass is 1 us of memory traffic, so what bounds it is latency:
+// of the loads (8 of a thread in flight together), of LDS adds to one address
+// (the first digit takes few values; eight copies of the histograms, by
+// lane), and of the launch.  Choosing the bin in the pass itself and the mass
+// mode's next larger key in its last pass leave 6 launches of 12 for a mass
+// threshold and 7 of 11 for a sample; the three selections of 1M Gaussians in
+// 4 views with the blur criterion: 205 -> 138 us.
+constexpr int kSelCopies = 8;
+template <int MODE>
+__global__ __launch_bounds__(kSelBlock) void k_sel_pass(Source src, uint8_t* ws, int pass, double q_or_keep,
+                                                     double* tau) {
+  constexpr bool MASS = MODE == kModeMass, TWO = MODE == kModeValue;
+  __shared__ uint32_t s_part[TWO ? 2 : 1][kSelBins * kSelCopies];
+  __shared__ double s_psum[MASS ? kSelBins * kSelCopies : 1];
+  __shared__ uint32_t s_cnt[2][kSelBins];
+  __shared__ double s_sum[MASS ? kSelBins : 1];
   __shared__ uint32_t s_min;
+  __shared__ bool s_last;
   const int p = blockIdx.y;
   SelState* st = sel_state(ws, p);
-  if (!st->need_above) return;  // uniform per block
+  const SelState now = *st;  // unchanged until the last workgroup's choice
+  // the first step's values are in flight while the histograms are cleared, the
+  // next step's while one is counted
+  int64_t i0 = (int64_t)blockIdx.x * kSelStep, i1;
+  float v[kSelBatch];
+  uint32_t m = src.take_many<kSelBatch, kSelBlock>(p, i0 + threadIdx.x, v);
+  for (int b = threadIdx.x; b < kSelBins * kSelCopies; b += kSelBlock) {
+    s_part[0][b] = 0u;
+    if (TWO) s_part[TWO ? 1 : 0][b] = 0u;
+    if (MASS) s_psum[b] = 0.0;
+  }
   if (threadIdx.x == 0) s_min = 0xFFFFFFFFu;
+  const int shift = 24 - 8 * pass;
+  const uint32_t hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (32 - 8 * pass));
+  const uint32_t pre0 = now.prefix[0], pre1 = now.prefix[1];
+  const bool two = TWO && pass > 0;
+  const bool find_above = MASS && pass == kSelPasses - 1;
+  const uint32_t copy = threadIdx.x & (kSelCopies - 1);
+  uint32_t above = 0xFFFFFFFFu;  // smallest key above the group of the target
   __syncthreads();
-  const uint32_t key0 = st->prefix[0];
-  uint32_t best = 0xFFFFFFFFu;
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < src.n; i += stride) {
-    float v;
-    if (!src.take(p, i, v)) continue;
-    const uint32_t k = order_key(v);
-    if (k > key0 && k < best) best = k;
+  for (; i0 < src.n; i0 = i1) {
+    i1 = i0 + (int64_t)gridDim.x * kSelStep;
+    float w[kSelBatch];
+    uint32_t mw = 0u;
+    if (i1 < src.n) mw = src.take_many<kSelBatch, kSelBlock>(p, i1 + threadIdx.x, w);
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      if (!((m >> u) & 1u)) continue;
+      const uint32_t k = order_key(v[u]);
+      const uint32_t d = ((k >> shift) & 0xFFu) * kSelCopies + copy;
+      if (((k ^ pre0) & hi_mask) == 0u) {
+        atomicAdd(&s_part[0][d], 1u);
+        if (MASS) atomicAdd(&s_psum[d], (double)v[u]);
+      } else if (find_above && k > pre0 && k < above) {
+        above = k;
+      }
+      if (two && ((k ^ pre1) & hi_mask) == 0u) atomicAdd(&s_part[TWO ? 1 : 0][d], 1u);
+    }
+    m = mw;
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) v[u] = w[u];
   }
-  atomicMin(&s_min, best);
+  if (find_above && above != 0xFFFFFFFFu) atomicMin(&s_min, above);
   __syncthreads();
-  if (threadIdx.x == 0 && s_min != 0xFFFFFFFFu) atomicMin(&st->min_above, s_min);
-}
-
-template <int MODE>
-__global__ __launch_bounds__(kWave) void k_sel_finish(uint8_t* ws, double* tau) {
-  constexpr bool MASS = MODE == kModeMass;
-  const int p = blockIdx.x;
-  const SelState* st = sel_state(ws, p);
-  if (threadIdx.x != 0) return;
-  double t;
-  if (st->m == 0 || (MODE == kModeRank && st->rank[0] < 0)) {
-    t = __builtin_nan("");
-  } else if (MODE == kModeRank) {
-    t = (double)key_value(st->prefix[0]);
-  } else if (MASS) {
-    t = (double)key_value(st->need_above ? st->min_above : st->prefix[0]);
-  } else {
-    // a + frac (b - a)
-    const double a = (double)key_value(st->prefix[0]);
-    const double b = (double)key_value(st->prefix[1]);
-    const double prod = st->frac * (b - a);
-    t = a + prod;
+  SelHist* h = sel_hist(ws, p);
+  static_assert(kSelBlock >= 3 * kSelBins, "a bin of one histogram per thread");
+  const int part = threadIdx.x / kSelBins, b = threadIdx.x % kSelBins;
+  {
+    // The adds return the old value, and a workgroup counts itself as done when
+    // it holds them: its adds have then taken effect for the whole device, which
+    // the last workgroup reads with device-wide loads.  (A __threadfence here
+    // writes back the L2 from every wave: 44 us per pass instead of 7 to 13.)
+    uint32_t old = 0u;
+    double old_sum = 0.0;
+    if (part == 0 || (TWO && part == 1)) {
+      uint32_t c = 0;
+#pragma unroll
+      for (int q = 0; q < kSelCopies; ++q) c += s_part[TWO ? part : 0][b * kSelCopies + q];
+      if (c) old = atomicAdd(&h->cnt[part][b], c);
+    } else if (MASS && part == 1) {
+      double sum = 0.0;
+#pragma unroll
+      for (int q = 0; q < kSelCopies; ++q) sum += s_psum[MASS ? b * kSelCopies + q : 0];
+      if (sum != 0.0) old_sum = atomicAdd(&h->sum[b], sum);
+    } else if (find_above && part == 2 && b == 0 && s_min != 0xFFFFFFFFu) {
+      old = atomicMin(&st->min_above, s_min);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(old), "v"(old_sum) : "memory");
   }
-  tau[p] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(&st->done, 1u) == gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  if (part < 2) {
+    // read, and clear for the next pass
+    s_cnt[part][b] = __hip_atomic_load(&h->cnt[part][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    h->cnt[part][b] = 0u;
+  } else if (part == 2) {
+    if (MASS) {
+      s_sum[b] = __hip_atomic_load(&h->sum[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      h->sum[b] = 0.0;
+    }
+  } else if (b == 0) {
+    s_min = __hip_atomic_load(&st->min_above, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    st->done = 0u;
+    st->min_above = 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  if (threadIdx.x < kWave) sel_step<MODE>(now, st, s_cnt, s_sum, s_min, pass, q_or_keep, tau + p);
 }
 
 __global__ __launch_bounds__(kBlock) void k_sel_apply(Source src, const double* __restrict__ tau,
                                                       uint8_t* __restrict__ out) {
   const int p = blockIdx.y;
   const double t = tau[p];
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < src.n; i += stride) {
-    float v;
-    const bool s = src.take(p, i, v);
-    out[(int64_t)p * src.n + i] = (s && (double)v > t) ? 1 : 0;
+  for (int64_t base = (int64_t)blockIdx.x * kApplyChunk; base < src.n; base += (int64_t)gridDim.x * kApplyChunk) {
+#pragma unroll 1
+    for (int h = 0; h < kApplyChunk; h += kBlock * kSelBatch) {
+      const int64_t i = base + h + threadIdx.x;
+      float v[kSelBatch];
+      const uint32_t m = src.take_many<kSelBatch>(p, i, v);
+#pragma unroll
+      for (int u = 0; u < kSelBatch; ++u)
+        if (i + u * kBlock < src.n)
+          out[(int64_t)p * src.n + i + u * kBlock] = (((m >> u) & 1u) && (double)v[u] > t) ? 1 : 0;
+    }
   }
 }
 
+// Workgroups per problem of a pass.  One step each while that leaves at most
+// one workgroup per CU; beyond, two steps each, since every workgroup adds its
+// bins to the problem's in memory (1M values: one problem 9.4 us a pass with
+// two steps and 7.6 with one; four problems 10.8 us with two and 12.2 with one).
 int32_t sel_blocks(int64_t n, int P) {
-  int64_t b = (n + (int64_t)kBlock * 16 - 1) / ((int64_t)kBlock * 16);
+  const int64_t steps = n > 0 ? (n + kSelStep - 1) / kSelStep : 1;
+  const int64_t b = steps * P <= 256 ? steps : (steps + 1) / 2;
+  return (int32_t)(b < 256 ? b : 256);
+}
+int32_t apply_blocks(int64_t n, int P) {
+  int64_t b = (n + kApplyChunk - 1) / kApplyChunk;
   const int64_t cap = P > 1 ? 256 : 1024;
   if (b > cap) b = cap;
   return (int32_t)(b < 1 ? 1 : b);
@@ -410,27 +490,15 @@ int32_t launch_threshold(const Source& src, int P, double keep, int32_t mode, ui
   const bool mass = mode == GS_THRESHOLD_MASS;
   const double param = mass ? keep : 1.0 - keep;
   const dim3 grid((unsigned)sel_blocks(src.n, P), (unsigned)P);
+  const dim3 agrid((unsigned)apply_blocks(src.n, P), (unsigned)P);
   hipLaunchKernelGGL(k_sel_init, dim3(P), dim3(kBlock), 0, st, w);
   MS_CHECK_LAUNCH("sel_init");
   for (int pass = 0; pass < kSelPasses; ++pass) {
-    if (mass) {
-      hipLaunchKernelGGL(k_sel_hist<kModeMass>, grid, dim3(kBlock), 0, st, src, w, pass);
-      hipLaunchKernelGGL(k_sel_step<kModeMass>, dim3(P), dim3(kBlock), 0, st, w, pass, param);
-    } else {
-      hipLaunchKernelGGL(k_sel_hist<kModeValue>, grid, dim3(kBlock), 0, st, src, w, pass);
-      hipLaunchKernelGGL(k_sel_step<kModeValue>, dim3(P), dim3(kBlock), 0, st, w, pass, param);
-    }
+    if (mass) hipLaunchKernelGGL(k_sel_pass<kModeMass>, grid, dim3(kSelBlock), 0, st, src, w, pass, param, tau);
+    else hipLaunchKernelGGL(k_sel_pass<kModeValue>, grid, dim3(kSelBlock), 0, st, src, w, pass, param, tau);
     MS_CHECK_LAUNCH("sel_pass");
   }
-  if (mass) {
-    hipLaunchKernelGGL(k_sel_group, dim3(P), dim3(kBlock), 0, st, w);
-    hipLaunchKernelGGL(k_sel_min_above, grid, dim3(kBlock), 0, st, src, w);
-    hipLaunchKernelGGL(k_sel_finish<kModeMass>, dim3(P), dim3(kWave), 0, st, w, tau);
-  } else {
-    hipLaunchKernelGGL(k_sel_finish<kModeValue>, dim3(P), dim3(kWave), 0, st, w, tau);
-  }
-  MS_CHECK_LAUNCH("sel_finish");
-  hipLaunchKernelGGL(k_sel_apply, grid, dim3(kBlock), 0, st, src, tau, out);
+  hipLaunchKernelGGL(k_sel_apply, agrid, dim3(kBlock), 0, st, src, tau, out);
   MS_CHECK_LAUNCH("sel_apply");
   return GS_OK;
 }
@@ -682,16 +750,23 @@ __global__ __launch_bounds__(kBlock) void k_split_write(ClonePlanes in, const ui
 // ---------------------------------------------------------------------------
 // primitive sampling: the k smallest exponential keys, ties by lower index
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_tie_count(Source src, const double* __restrict__ tau,
+// Counted only where a part of the ties is taken: the first of them by index.
+static_assert(kCloneItems % (kBlock * kSelBatch) == 0, "whole batches per workgroup");
+__global__ __launch_bounds__(kBlock) void k_tie_count(Source src, const uint8_t* __restrict__ ws,
+                                                      const double* __restrict__ tau,
                                                       uint32_t* __restrict__ block_cnt) {
   __shared__ uint32_t s_part[kBlock / kWave];
   const double t = *tau;
   const int64_t base = (int64_t)blockIdx.x * kCloneItems;
   uint32_t c = 0;
-  for (int j = threadIdx.x; j < kCloneItems; j += kBlock) {
-    const int64_t i = base + j;
-    float v;
-    if (i < src.n && src.take(0, i, v) && (double)v == t) ++c;
+  if (((const SelState*)ws)->all_ties == 0) {
+#pragma unroll 1
+    for (int j = 0; j < kCloneItems; j += kBlock * kSelBatch) {
+      float v[kSelBatch];
+      const uint32_t m = src.take_many<kSelBatch>(0, base + j + threadIdx.x, v);
+#pragma unroll
+      for (int u = 0; u < kSelBatch; ++u) c += ((m >> u) & 1u) && (double)v[u] == t ? 1u : 0u;
+    }
   }
   for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
   if (lane_id() == 0) s_part[threadIdx.x / kWave] = c;
@@ -703,34 +778,51 @@ __global__ __launch_bounds__(kBlock) void k_sample_write(Source src, const uint8
                                                          const double* __restrict__ tau,
                                                          const uint32_t* __restrict__ block_off, int64_t k,
                                                          uint8_t* __restrict__ out, int64_t* __restrict__ count) {
-  __shared__ uint32_t s_wave[kBlock / kWave];
-  __shared__ uint32_t s_carry;
+  __shared__ uint32_t s_wave[kSelBatch][kBlock / kWave];
   const SelState* st = (const SelState*)ws;
   const double t = *tau;
   const int64_t take_ties = st->rank[0] + 1;  // ties at tau taken, in index order
+  const bool all_ties = st->all_ties != 0;
   const int64_t base = (int64_t)blockIdx.x * kCloneItems;
-  if (threadIdx.x == 0) s_carry = block_off[blockIdx.x];
+  uint32_t carry = block_off[blockIdx.x];
   if (blockIdx.x == 0 && threadIdx.x == 0) *count = (st->m == 0 || k <= 0) ? 0 : (k < st->m ? k : st->m);
-  __syncthreads();
-  for (int j0 = 0; j0 < kCloneItems; j0 += kBlock) {
+#pragma unroll 1
+  for (int j0 = 0; j0 < kCloneItems; j0 += kBlock * kSelBatch) {
     const int64_t i = base + j0 + threadIdx.x;
-    float v = 0.0f;
-    const bool s = i < src.n && src.take(0, i, v);
-    const bool tie = s && (double)v == t;
-    const uint64_t bal = __ballot(tie);
-    const uint32_t below = __popcll(bal & ((1ull << lane_id()) - 1ull));
-    if (lane_id() == 0) s_wave[threadIdx.x / kWave] = (uint32_t)__popcll(bal);
-    __syncthreads();
-    uint32_t off = s_carry;
-    for (int w = 0; w < (int)(threadIdx.x / kWave); ++w) off += s_wave[w];
-    const uint32_t chunk = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-    if (i < src.n) {
-      const bool sel = s && ((double)v < t || (tie && (int64_t)(off + below) < take_ties));
-      out[i] = sel ? 1 : 0;
+    float v[kSelBatch];
+    const uint32_t m = src.take_many<kSelBatch>(0, i, v);
+    uint32_t ties = 0u, taken = 0u;
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      const bool s = (m >> u) & 1u;
+      ties |= s && (double)v[u] == t ? 1u << u : 0u;
+      taken |= s && (double)v[u] < t ? 1u << u : 0u;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) s_carry += chunk;
-    __syncthreads();
+    if (all_ties) {
+      taken |= ties;
+    } else {
+      uint32_t below[kSelBatch];
+#pragma unroll
+      for (int u = 0; u < kSelBatch; ++u) {
+        const uint64_t bal = __ballot((ties >> u) & 1u);
+        below[u] = __popcll(bal & ((1ull << lane_id()) - 1ull));
+        if (lane_id() == 0) s_wave[u][threadIdx.x / kWave] = (uint32_t)__popcll(bal);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kSelBatch; ++u) {
+        uint32_t off = carry + below[u];
+        for (int w = 0; w < kBlock / kWave; ++w) {
+          off += w < (int)(threadIdx.x / kWave) ? s_wave[u][w] : 0u;
+          carry += s_wave[u][w];
+        }
+        if (((ties >> u) & 1u) && (int64_t)off < take_ties) taken |= 1u << u;
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u)
+      if (i + u * kBlock < src.n) out[i + u * kBlock] = (taken >> u) & 1u;
   }
 }
 
@@ -980,14 +1072,11 @@ int32_t gs_sample(const float* importance, const uint32_t* area, const float* ex
   hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(kBlock), 0, st, w);
   MS_CHECK_LAUNCH("sample_init");
   for (int pass = 0; pass < kSelPasses; ++pass) {
-    hipLaunchKernelGGL(k_sel_hist<kModeRank>, grid, dim3(kBlock), 0, st, src, w, pass);
-    hipLaunchKernelGGL(k_sel_step<kModeRank>, dim3(1), dim3(kBlock), 0, st, w, pass, (double)k);
+    hipLaunchKernelGGL(k_sel_pass<kModeRank>, grid, dim3(kSelBlock), 0, st, src, w, pass, (double)k, tau);
     MS_CHECK_LAUNCH("sample_pass");
   }
-  hipLaunchKernelGGL(k_sel_finish<kModeRank>, dim3(1), dim3(kWave), 0, st, w, tau);
-  MS_CHECK_LAUNCH("sample_finish");
   if (nb > 0) {
-    hipLaunchKernelGGL(k_tie_count, dim3(nb), dim3(kBlock), 0, st, src, tau, block_off);
+    hipLaunchKernelGGL(k_tie_count, dim3(nb), dim3(kBlock), 0, st, src, w, tau, block_off);
     MS_CHECK_LAUNCH("sample_ties");
   }
   hipLaunchKernelGGL(k_clone_scan, dim3(1), dim3(1024), 0, st, block_off, nb, ties);
