@@ -337,7 +337,7 @@ __device__ __forceinline__ void sel_step(const SelState& now, SelState* st, cons
 // (the first digit takes few values; eight copies of the histograms, by
 // lane), and of the launch.  Choosing the bin in the pass itself and the mass
 // mode's next larger key in its last pass leave 6 launches of 12 for a mass
-// threshold and 7 of 11 for a sample; the three selections of 1M Gaussians in
+// threshold and 8 of 13 for a sample; the three selections of 1M Gaussians in
 // 4 views with the blur criterion: 205 -> 138 us.
 constexpr int kSelCopies = 8;
 template <int MODE>
