@@ -326,6 +326,9 @@ void gs_sort_set_spin_limit(uint32_t polls);
  * for another value. */
 enum { GS_SORT_PRESCAN = 0, GS_SORT_LOOKBACK = 1 };
 int32_t gs_sort_set_algorithm(int32_t algorithm);
+/* 1 when sorts enqueued now wait on other workgroups, so that their status
+ * flag (gs_sort_status) can be raised: the look-back sort.  0 otherwise. */
+int32_t gs_sort_waits(void);
 
 /* Diagnostic: the largest number of 4096-record blocks for which gs_bin_count
  * runs two kernels (each block of the down-sweep adds the totals of the

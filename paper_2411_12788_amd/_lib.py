@@ -96,6 +96,7 @@ _SIGS = {
     "gs_sort_pairs": (c_i32, [c_p, c_p, c_i64, c_i32, c_p, c_sz, c_p]),
     "gs_tile_ranges": (c_i32, [c_p, c_i64, c_i32, c_u32, c_i32, c_p, c_p, c_p]),
     "gs_sort_status": (c_i32, [c_p, c_p]),
+    "gs_sort_waits": (c_i32, []),
     "gs_sort_set_spin_limit": (None, [c_u32]),
     "gs_sort_set_algorithm": (c_i32, [c_i32]),
     "gs_bin_count_set_fold_blocks": (c_i64, [c_i64]),

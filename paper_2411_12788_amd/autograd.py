@@ -29,6 +29,8 @@ class RasterizeFn(torch.autograd.Function):
     @staticmethod
     def forward(ctx, means, scales, quats, opacity, sh, cams, opts, sh_degree, active, save_lists, accum,
                 deterministic):
+        cams = R.cameras(cams)  # once for all stages and the backward
+        ctx.set_materialize_grads(False)  # no zero tensors for depth and index
         scene = R.DeviceScene(means.contiguous(), scales.contiguous(), quats.contiguous(), opacity.contiguous(),
                               sh.contiguous(), int(sh_degree))
         proj = R.project(scene, cams, opts)
@@ -53,6 +55,8 @@ class RasterizeFn(torch.autograd.Function):
             proj = R.project(scene, ctx.cams, ctx.opts)
             binned = R.bin(proj, ctx.cams, scene.n)
         frame = R.Frame(None, None, None, t_final, last, None, None)
+        if dcolor is None:
+            dcolor = torch.zeros((3, t_final.numel()), device=t_final.device)
         grads, _ = R.render_backward(scene, proj, binned, ctx.cams, ctx.opts, frame, dcolor.contiguous(),
                                      ctx.active, deterministic=ctx.deterministic)
         ctx.lists = None

@@ -489,6 +489,8 @@ int32_t gs_sort_status(const void* ws, void* stream) {
   return GS_OK;
 }
 
+int32_t gs_sort_waits(void) { return sort_is_prescan() ? 0 : 1; }
+
 void gs_sort_set_spin_limit(uint32_t polls) { g_spin_limit.store(polls); }
 
 int32_t gs_sort_set_algorithm(int32_t algorithm) {

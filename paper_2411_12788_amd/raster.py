@@ -20,6 +20,10 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream=None):
+    if stream is None and torch.cuda.is_initialized():
+        # the current stream's handle without building a Stream object (14 us,
+        # once per library call)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
 
@@ -96,6 +100,11 @@ class DeviceScene:
 
 
 def cameras(cams) -> "ctypes.Array[L.Camera]":
+    """The library's camera array of `cams`; an array that is one already is
+    returned as it is, so a caller of several stages can build it once and
+    pass it as their `cams`."""
+    if isinstance(cams, ctypes.Array) and cams._type_ is L.Camera:
+        return cams
     arr = (L.Camera * len(cams))()
     for k, c in enumerate(cams):
         Rm = np.asarray(c.R, dtype=np.float32).reshape(9)
@@ -314,10 +323,15 @@ def sort_status(ws: torch.Tensor, stream=None) -> None:
 
 def bin(proj: Projected, cams, n: int, want_keys: bool = False, stream=None, check: bool = True) -> Binned:
     """Pair count, key emission, sort and ranges; with `check` the sort's
-    status flag is read back (one synchronisation)."""
+    status flag is read back (one synchronisation) where it can be raised: by
+    the look-back sort, whose workgroups wait for each other.  The default
+    sort and the lists made by tile wait on nobody, and nothing is read back
+    (33 us of a training step of 4k Gaussians, twice).  With an explicit
+    `stream` it always is: the workspaces belong to the current stream and may
+    be reused there once this returns."""
     buffers = StepBuffers()
     out = bin_step(proj, cams, n, buffers, want_keys, stream)
-    if check:
+    if check and (stream is not None or L.lib().gs_sort_waits()):
         sort_status(buffers.bins.ws, stream)
     return out
 
