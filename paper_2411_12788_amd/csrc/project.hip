@@ -74,15 +74,18 @@ struct Geo {
   bool ok;
 };
 
-__device__ __forceinline__ void geometry(const KView& cam, const KOpts& op, const SceneArgs& sc, int64_t i, Geo& g) {
-  const int64_t n = sc.n;
-  const double p0 = sc.means[i], p1 = sc.means[n + i], p2 = sc.means[2 * n + i];
+// Its parts: centre (one view), rotation and scales (no view enters), and the
+// rest of a view.
+__device__ __forceinline__ void geometry_centre(const KView& cam, const KOpts& op, const double* p, Geo& g) {
   double R[9];
   for (int k = 0; k < 9; ++k) R[k] = cam.R[k];
-  g.t[0] = R[0] * p0 + R[1] * p1 + R[2] * p2 + (double)cam.t[0];
-  g.t[1] = R[3] * p0 + R[4] * p1 + R[5] * p2 + (double)cam.t[1];
-  g.t[2] = R[6] * p0 + R[7] * p1 + R[8] * p2 + (double)cam.t[2];
+  g.t[0] = R[0] * p[0] + R[1] * p[1] + R[2] * p[2] + (double)cam.t[0];
+  g.t[1] = R[3] * p[0] + R[4] * p[1] + R[5] * p[2] + (double)cam.t[1];
+  g.t[2] = R[6] * p[0] + R[7] * p[1] + R[8] * p[2] + (double)cam.t[2];
   g.ok = g.t[2] > (double)op.znear;
+}
+__device__ __forceinline__ void geometry_scene(const SceneArgs& sc, int64_t i, Geo& g) {
+  const int64_t n = sc.n;
   const double qw = sc.quats[i], qx = sc.quats[n + i], qy = sc.quats[2 * n + i], qz = sc.quats[3 * n + i];
   const double qn2 = qw * qw + qx * qx + qy * qy + qz * qz;
   g.ok = g.ok && qn2 > 0.0;
@@ -94,6 +97,10 @@ __device__ __forceinline__ void geometry(const KView& cam, const KOpts& op, cons
   g.Rq[1][0] = 2.0 * (x * y + w * z); g.Rq[1][1] = 1.0 - 2.0 * (x * x + z * z); g.Rq[1][2] = 2.0 * (y * z - w * x);
   g.Rq[2][0] = 2.0 * (x * z - w * y); g.Rq[2][1] = 2.0 * (y * z + w * x); g.Rq[2][2] = 1.0 - 2.0 * (x * x + y * y);
   g.s[0] = sc.scales[i]; g.s[1] = sc.scales[n + i]; g.s[2] = sc.scales[2 * n + i];
+}
+__device__ __forceinline__ void geometry_view(const KView& cam, const KOpts& op, Geo& g) {
+  double R[9];
+  for (int k = 0; k < 9; ++k) R[k] = cam.R[k];
   // camera-frame axes of the ellipsoid: columns of W Rq, scaled by s
   double A[3][3];
   for (int r = 0; r < 3; ++r)
@@ -125,11 +132,25 @@ __device__ __forceinline__ void geometry(const KView& cam, const KOpts& op, cons
   g.v = fy * g.t[1] / tz + (double)cam.cy;
 }
 
+__device__ __forceinline__ void geometry(const KView& cam, const KOpts& op, const SceneArgs& sc, int64_t i, Geo& g) {
+  const double p[3] = {sc.means[i], sc.means[sc.n + i], sc.means[2 * sc.n + i]};
+  geometry_centre(cam, op, p, g);
+  geometry_scene(sc, i, g);
+  geometry_view(cam, op, g);
+}
+
 __device__ __forceinline__ void camera_centre(const KView& cam, double* c) {
   for (int k = 0; k < 3; ++k)
     c[k] = -((double)cam.R[k] * cam.t[0] + (double)cam.R[3 + k] * cam.t[1] + (double)cam.R[6 + k] * cam.t[2]);
 }
 
+// Several views of at least this many Gaussians: one thread per Gaussian
+// (k_project_views) instead of one per record.  Below, one thread per record
+// has the waves to hide its latency: 32,768 Gaussians in 8 views 18 us against
+// 22, in 16 views 27 against 36; 65,536 in 8 views 28 against 24, in 16 views 46
+// against 39; with 2 to 4 views both are alike there and 3 to 24 % apart at
+// 500,000 and more.
+constexpr int64_t kViewsMinRows = 1 << 16;
 struct ProjArgs {
   SceneArgs sc;
   const uint8_t* cull;
@@ -139,29 +160,18 @@ struct ProjArgs {
   float tile_cull;  // log2 of the tile-culling alpha, or 0 (off)
 };
 
-// One thread per record.  Bound by memory: a Gaussian's 236 bytes once, 80
-// bytes per record.  The views of one block of Gaussians are projected by
-// consecutive workgroups of one XCD (workgroups go to the eight XCDs in turn),
-// so only the first of them reads the block from HBM and the others find it
-// in that XCD's L2; with the views one after the other the scene was read
-// once per view (1M Gaussians, 16 views in two calls: 1467 -> 1180 us).
-template <int DEG>
-__global__ __launch_bounds__(kBlock) void k_project(ProjArgs pa, ViewSet vs) {
-  const uint32_t turn = blockIdx.x >> 3, group = turn / (uint32_t)vs.count;
-  const int v = (int)(turn - group * (uint32_t)vs.count);
-  const int64_t i = ((int64_t)group * 8 + (blockIdx.x & 7)) * kBlock + threadIdx.x;
-  const int64_t n = pa.sc.n;
-  if (i >= n) return;
-  const KView& cam = vs.v[v];
+// One record: geometry g in view `cam`, opacity o, to row r.  log_ratio():
+// 2 ln(o / alpha_min); p(k): the centre; fetch_sh() runs before the first sh(k),
+// plane k of the SH coefficients, and only for a record drawn.
+template <int DEG, typename Kk, typename Centre, typename Fetch, typename Sh>
+__device__ __forceinline__ void project_record(const ProjArgs& pa, const KView& cam, int64_t r, const Geo& g, double o,
+                                               const Kk& log_ratio, const Centre& p, bool culled,
+                                               const Fetch& fetch_sh, const Sh& sh) {
   const KOpts& op = pa.op;
-  const int64_t r = (int64_t)v * n + i;
-  Geo g;
-  geometry(cam, op, pa.sc, i, g);
-  const double o = pa.sc.opacity[i];
   bool ok = g.ok && o >= (double)op.alpha_min;
-  if (pa.cull && pa.cull[i] == 0) ok = false;
+  if (culled) ok = false;
   // extent of the ellipse where opacity * G2D >= alpha_min
-  const double kk = 2.0 * log(o / (double)op.alpha_min);
+  const double kk = log_ratio();
   const double ex = sqrt(kk * g.S00), ey = sqrt(kk * g.S11);
   ok = ok && isfinite(g.u) && isfinite(g.v) && isfinite(ex) && isfinite(ey) && isfinite(g.a) && isfinite(g.b) &&
        isfinite(g.c) && isfinite(g.t[2]);
@@ -184,15 +194,15 @@ __global__ __launch_bounds__(kBlock) void k_project(ProjArgs pa, ViewSet vs) {
   // together) are not read at all.
   double rgb[3] = {0.5, 0.5, 0.5};
   if (ok) {
+    fetch_sh();
     double cc[3];
     camera_centre(cam, cc);
-    double dx = pa.sc.means[i] - cc[0], dy = pa.sc.means[n + i] - cc[1], dz = pa.sc.means[2 * n + i] - cc[2];
+    double dx = p(0) - cc[0], dy = p(1) - cc[1], dz = p(2) - cc[2];
     const double il = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
     dx *= il; dy *= il; dz *= il;
-    const float* shp = pa.sc.sh;
     sh_terms<DEG>(dx, dy, dz, [&](int k, double Yk, double, double, double) {
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) rgb[ch] += (double)shp[(int64_t)(k * 3 + ch) * n + i] * Yk;
+      for (int ch = 0; ch < 3; ++ch) rgb[ch] += (double)sh(k * 3 + ch) * Yk;
     });
     // a colour that is not finite before the clamp (NaN or infinite SH terms)
     // makes the record invalid; the clamp must not turn NaN into black
@@ -233,6 +243,75 @@ __global__ __launch_bounds__(kBlock) void k_project(ProjArgs pa, ViewSet vs) {
   b4.z = (int32_t)__float_as_uint(zf);
   b4.w = tiles;
   reinterpret_cast<int4*>(pa.bin)[r] = b4;
+}
+
+// One thread per record.  Bound by memory: a Gaussian's 236 bytes once, 80
+// bytes per record.  The views of one block of Gaussians are projected by
+// consecutive workgroups of one XCD (workgroups go to the eight XCDs in turn),
+// so only the first of them reads the block from HBM and the others find it
+// in that XCD's L2; with the views one after the other the scene was read
+// once per view (1M Gaussians in 16 views, which k_project_views takes now:
+// 1467 us against 1180).
+template <int DEG>
+__global__ __launch_bounds__(kBlock) void k_project(ProjArgs pa, ViewSet vs) {
+  const uint32_t turn = blockIdx.x >> 3, group = turn / (uint32_t)vs.count;
+  const int v = (int)(turn - group * (uint32_t)vs.count);
+  const int64_t i = ((int64_t)group * 8 + (blockIdx.x & 7)) * kBlock + threadIdx.x;
+  const int64_t n = pa.sc.n;
+  if (i >= n) return;
+  const KView& cam = vs.v[v];
+  const int64_t r = (int64_t)v * n + i;
+  Geo g;
+  geometry(cam, pa.op, pa.sc, i, g);
+  const double o = pa.sc.opacity[i];
+  const float* shp = pa.sc.sh;
+  project_record<DEG>(
+      pa, cam, r, g, o, [&] { return 2.0 * log(o / (double)pa.op.alpha_min); },
+      [&](int k) { return (double)pa.sc.means[k * n + i]; }, pa.cull && pa.cull[i] == 0, [] {},
+      [&](int k) { return shp[(int64_t)k * n + i]; });
+}
+
+// One thread per Gaussian, its views one after the other: what no view enters
+// (rotation, logarithms, 59 loads and their conversions) is done once, and the
+// SH coefficients stay in registers from the first view that draws it: 256
+// VGPRs, two waves per SIMD, which the independent double instructions of a
+// record (its bound now) keep busy.  Reading the coefficients again for each
+// view at four waves instead spilled, 3626 us.  1M Gaussians, 16 views in two
+// calls: 1159 -> 784 us; 500k, 8 views: 179 -> 134 us.
+template <int DEG>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_project_views(ProjArgs pa,
+                                                                                                   ViewSet vs) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t n = pa.sc.n;
+  if (i >= n) return;
+  const double p[3] = {pa.sc.means[i], pa.sc.means[n + i], pa.sc.means[2 * n + i]};
+  Geo g;
+  g.ok = true;
+  geometry_scene(pa.sc, i, g);
+  const bool turned = g.ok;  // the quaternion is not zero
+  const double o = pa.sc.opacity[i];
+  const double kk = 2.0 * log(o / (double)pa.op.alpha_min);
+  const bool culled = pa.cull && pa.cull[i] == 0;
+  constexpr int kPlanes = 3 * (DEG + 1) * (DEG + 1);
+  float coef[kPlanes];
+#pragma unroll
+  for (int k = 0; k < kPlanes; ++k) coef[k] = 0.f;
+  bool have = false;
+#pragma unroll 1
+  for (int v = 0; v < vs.count; ++v) {
+    geometry_centre(vs.v[v], pa.op, p, g);
+    g.ok = g.ok && turned;
+    geometry_view(vs.v[v], pa.op, g);
+    project_record<DEG>(
+        pa, vs.v[v], (int64_t)v * n + i, g, o, [&] { return kk; }, [&](int k) { return p[k]; }, culled,
+        [&] {
+          if (have) return;
+          have = true;
+#pragma unroll
+          for (int k = 0; k < kPlanes; ++k) coef[k] = pa.sc.sh[(int64_t)k * n + i];
+        },
+        [&](int k) { return coef[k]; });
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -518,9 +597,20 @@ extern "C" int32_t gs_project(const gs_scene_t* scene, const gs_camera_t* cams, 
   pa.bin = out->bin;
   pa.op = make_kopts(opts);
   pa.tile_cull = out->tile_cull_log2_alpha < 0.f ? out->tile_cull_log2_alpha : 0.f;
+  hipStream_t s = (hipStream_t)stream;
+  if (V >= 2 && scene->n >= kViewsMinRows) {
+    const dim3 grid((unsigned)grid_1d(scene->n));
+    switch (scene->sh_degree) {
+      case 0: hipLaunchKernelGGL(k_project_views<0>, grid, dim3(kBlock), 0, s, pa, vs); break;
+      case 1: hipLaunchKernelGGL(k_project_views<1>, grid, dim3(kBlock), 0, s, pa, vs); break;
+      case 2: hipLaunchKernelGGL(k_project_views<2>, grid, dim3(kBlock), 0, s, pa, vs); break;
+      default: hipLaunchKernelGGL(k_project_views<3>, grid, dim3(kBlock), 0, s, pa, vs); break;
+    }
+    MS_CHECK_LAUNCH("project");
+    return GS_OK;
+  }
   const int64_t blocks = (grid_1d(scene->n) + 7) / 8 * 8 * V;  // n V < 2^32: fits
   const dim3 grid((unsigned)blocks);
-  hipStream_t s = (hipStream_t)stream;
   switch (scene->sh_degree) {
     case 0: hipLaunchKernelGGL(k_project<0>, grid, dim3(kBlock), 0, s, pa, vs); break;
     case 1: hipLaunchKernelGGL(k_project<1>, grid, dim3(kBlock), 0, s, pa, vs); break;
