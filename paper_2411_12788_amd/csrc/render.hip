@@ -925,48 +925,72 @@ __device__ __forceinline__ StagedB fetch_entry_bwd(const float* __restrict__ rec
   return e;
 }
 
-// Sum of nine per-lane partials over each 16-lane row.  Each step adds the
-// other half of the lanes and keeps one value in either half: lanes 8 apart
-// (a row rotate; values 2 j and 2 j + 1 share a register), then the two quads
-// of a half row (its mirror), then the lanes of a quad.  The halves are chosen
-// by the bank mask of the add itself (lanes of a disabled bank keep the
-// register's value), so a pair of values costs two instructions and no
-// selects, which the compiler cannot express: hence the assembly.  A DPP read
-// needs two instructions after the write of its register; the order below
-// keeps that distance.  Returned: in lane L of a row the total of value
-// sum_slot(L), where that is not negative.
+// The nine sums of an entry over each 16-lane row (4x4 pixels): of six per-lane
+// partials p, and of the weight w times the three channels of dL/dcolour.
+//
+// Partials: each step adds the other half of the lanes and keeps one value in
+// either half: lanes 8 apart (a row rotate; values 2 j and 2 j + 1 share a
+// register), then the two quads of a half row (its mirror), then the lanes of a
+// quad.  The halves are chosen by the bank mask of the add itself (lanes of a
+// disabled bank keep the register's value), so a pair of values costs two
+// instructions and no selects, which the compiler cannot express: hence the
+// assembly.  Channels: lane m of a quad sums channel m over the quad's pixels,
+// w of each pixel by a broadcast inside the quad times that pixel's channel m
+// (gm, the same for all entries), then the four quads are added: six
+// instructions instead of three products and ten.  A DPP read needs two
+// instructions after the write of its register; the order below keeps that
+// distance.  Returned: in lane L of a row the total of value sum_slot(L), where
+// that is not negative.
 __device__ __forceinline__ int sum_slot(int lane) {
-  const int q = (lane >> 2) & 3, t = 2 * (q & 1) + (q >> 1);  // quads hold values 0, 2, 1, 3 and 4, 6, 5, 7
-  const int r = lane & 3;
-  return r == 0 ? t : r == 1 ? 4 + t : (lane & 15) == 2 ? 8 : -1;
+  const int q = (lane >> 2) & 3, r = lane & 3;
+  if (r == 3) return 2 * (q & 1) + (q >> 1);  // quads hold values 0, 2, 1, 3
+  if (q == 0) return 6 + r;
+  return r == 0 && q < 3 ? 3 + q : -1;  // values 4 and 5 in the halves of the row
 }
-__device__ __forceinline__ float row_sum9(const float (&p)[9], int lane) {
-  float a, b, c, d, e, f, h;
+struct ChannelPixels {
+  float x[4];  // lane m of a quad: channel m of the quad's pixels
+};
+__device__ __forceinline__ ChannelPixels channel_pixels(float g0, float g1, float g2, int lane) {
+  ChannelPixels r;
+  const int m = lane & 3;
+#define MS_QUAD(k, ctrl) \
+  { \
+    const float a = dpp_take<ctrl>(g0), b = dpp_take<ctrl>(g1), c = dpp_take<ctrl>(g2); \
+    r.x[k] = m == 0 ? a : m == 1 ? b : m == 2 ? c : 0.f; \
+  }
+  MS_QUAD(0, 0x00)
+  MS_QUAD(1, 0x55)
+  MS_QUAD(2, 0xAA)
+  MS_QUAD(3, 0xFF)
+#undef MS_QUAD
+  return r;
+}
+__device__ __forceinline__ float row_sum9(const float (&p)[6], float w, const ChannelPixels& gm, int lane) {
+  float a, b, c, d, f, h;
   asm("s_nop 1\n\t"
-      "v_add_f32_dpp %0, %7, %7 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %2, %11, %11 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %3, %13, %13 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %0, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %1, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %2, %12, %12 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %3, %14, %14 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %6, %15, %15 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %5, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %6, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %5, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %6, %6, %6 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_mul_f32_dpp %5, %12, %13 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %1, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_fmac_f32_dpp %5, %12, %14 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_fmac_f32_dpp %5, %12, %15 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %4, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, %12, %16 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %5, %5, %5 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %5, %5, %5 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
-      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d), "=&v"(e), "=&v"(f), "=&v"(h)
-      : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7]), "v"(p[8]));
-  const int r = lane & 3;
-  return r == 0 ? e : r == 1 ? f : h;
+      "v_add_f32_dpp %5, %5, %5 row_ror:4 row_mask:0xf bank_mask:0xf"
+      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d), "=&v"(f), "=&v"(h)
+      : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(w), "v"(gm.x[0]), "v"(gm.x[1]),
+        "v"(gm.x[2]), "v"(gm.x[3]));
+  return (lane & 3) == 3 ? d : (lane & 12) == 0 ? h : f;
 }
 
 // The nine sums of an entry over pixels, with e = dL/dalpha alpha (0 where
@@ -1003,12 +1027,13 @@ template <bool DET, typename Acc>
 __device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ part, uint32_t* __restrict__ pmask,
                                              uint32_t k, uint32_t base, int g16, int slot, uint64_t cm, int grp,
                                              float val) {
-  if (slot < 0 || ((cm >> (16 * grp)) & 0xffffull) == 0) return;
+  if (slot < 0) return;
   if (DET) {
+    if (((cm >> (16 * grp)) & 0xffffull) == 0) return;
     const uint32_t j = base + k;
     part[((int64_t)j * 16 + g16) * kG2d + slot] = val;
     if (slot == 8) atomicOr(pmask + j, 1u << g16);
-  } else {
+  } else if (val != 0.f) {
     atomicAdd(s_acc + (uint32_t)__umul24(k, (uint32_t)kG2d) + slot, (Acc)val);
   }
 }
@@ -1029,7 +1054,9 @@ __device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ par
 // (1M Gaussians, 16 views, 17.3M pixels, all active: 169M -> 31M requests).
 // Now bound by the vector instructions of the walk.  Measured there: with
 // those sums, list streams and the scalar suffix 9.76 -> 6.42 ms; with the
-// tests in the staging thread 5.80 ms; with double accumulators 4.34 ms.
+// tests in the staging thread 5.80 ms; with double accumulators 4.34 ms; with
+// the channel sums and tests of row_sum9 and emit_partial (64 vector
+// instructions per walked entry instead of 80) 4.08 ms.
 template <bool MASKED, bool DET>
 __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
                                                        const uint32_t* __restrict__ vals,
@@ -1088,6 +1115,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   lst = lst < end - start ? lst : end - start;  // `last` never exceeds the tile's list
   float S = T * (g0 * op.bg[0] + g1 * op.bg[1] + g2 * op.bg[2]);  // dL/dcolour . colour composited behind
   const int slot = sum_slot(lane);  // the sum this lane emits after row_sum9, or -1
+  const ChannelPixels gm = channel_pixels(g0, g1, g2, lane);
   {
     uint32_t m = lst;  // over the 16 lanes of a group; split rows hold the same pixels
 #pragma unroll
@@ -1157,7 +1185,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
         const float G2 = __builtin_amdgcn_exp2f(ee);
         const bool inc = val && ee >= op.log2_alpha_min;
-        const bool act = inc && c4.w > 0.f;
+        const bool act = MASKED ? inc && c4.w > 0.f : inc;
         const float al = fminf(op.alpha_max, G2);
         const float iom = __builtin_amdgcn_rcpf(1.f - al);
         const RowScan tr = rows_scan_mul(inc ? iom : 1.f, grp);
@@ -1166,11 +1194,8 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const float cg = g0 * c4.x + g1 * c4.y + g2 * c4.z;
         const RowScan us = rows_scan_add(wgt * cg, grp);
         const float ga = Tr * cg - (S + us.excl) * iom;
-        float pv[9];
-        const float wa = act ? wgt : 0.f;
-        pv[6] = wa * g0;
-        pv[7] = wa * g1;
-        pv[8] = wa * g2;
+        float pv[6];
+        const float wa = !MASKED || act ? wgt : 0.f;
         const float gal = (act && G2 < op.alpha_max) ? ga * al : 0.f;
         pv[5] = gal;
         pv[0] = gal * dx;
@@ -1180,20 +1205,22 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         pv[4] = pv[1] * dy;
         T = T * tr.total;
         S += us.total;
-        const uint64_t cm = __builtin_amdgcn_ballot_w64(act);
-        if (cm != 0) emit_partial<DET>(s_acc, part, pmask, off >> 4, base, g16, slot, cm, grp, row_sum9(pv, lane));
+        // (a weight is positive wherever the entry is composited)
+        const uint64_t cm = __builtin_amdgcn_ballot_w64(wa > 0.f);
+        if (cm != 0)
+          emit_partial<DET>(s_acc, part, pmask, off >> 4, base, g16, slot, cm, grp, row_sum9(pv, wa, gm, lane));
       }
       // One entry of the group's stream per iteration, latest first; the
       // transmittance is restored through them in reverse order.
       const int mine = grp == 0 ? n4[0] : grp == 1 ? n4[1] : grp == 2 ? n4[2] : n4[3];
       const int longest = rp ? 0 : max4(n4);
       const uint8_t* sp = &s_stream[wv][grp][0] + (mine > 0 ? mine - 1 : 0);
-      uint32_t off = (uint32_t)*sp * 16u;
+      uint32_t ahead = *sp;
       for (int i = 0; i < longest; ++i) {
-        const uint32_t at = off;
+        const uint32_t k = (uint32_t)fresh((int)ahead), at = k * 16u;
         const bool val = i < mine && at < lim;
         sp -= i + 1 < mine ? 1 : 0;
-        off = (uint32_t)*sp * 16u;
+        ahead = *sp;
         const float4 r0 = lds_at(s_r0, at), r1 = lds_at(s_r1, at), c4 = lds_at(s_r2, at);
         const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
         const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
@@ -1203,7 +1230,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         // finite, so the zero products are zeros.  Transmittance in front of
         // the entry, its partials, then its colour joins the suffix.
         const bool inc = val && ee >= op.log2_alpha_min;
-        const bool act = inc && c4.w > 0.f;
+        const bool act = MASKED ? inc && c4.w > 0.f : inc;
         const float al = fminf(op.alpha_max, G2);
         const float iom = __builtin_amdgcn_rcpf(1.f - al);
         T = inc ? T * iom : T;
@@ -1211,13 +1238,10 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const float cg = g0 * c4.x + g1 * c4.y + g2 * c4.z;
         const float ga = T * cg - S * iom;
         S += wgt * cg;
-        const uint64_t cm = __builtin_amdgcn_ballot_w64(act);
+        const float wa = !MASKED || act ? wgt : 0.f;
+        const uint64_t cm = __builtin_amdgcn_ballot_w64(wa > 0.f);
         if (cm == 0) continue;
-        float pv[9];
-        const float wa = act ? wgt : 0.f;
-        pv[6] = wa * g0;
-        pv[7] = wa * g1;
-        pv[8] = wa * g2;
+        float pv[6];
         // the clamped alpha has no gradient with respect to opacity or shape
         const float gal = (act && G2 < op.alpha_max) ? ga * al : 0.f;
         pv[5] = gal;
@@ -1226,7 +1250,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         pv[2] = pv[0] * dx;
         pv[3] = pv[0] * dy;
         pv[4] = pv[1] * dy;
-        emit_partial<DET>(s_acc, part, pmask, at >> 4, base, g16, slot, cm, grp, row_sum9(pv, lane));
+        emit_partial<DET>(s_acc, part, pmask, k, base, g16, slot, cm, grp, row_sum9(pv, wa, gm, lane));
       }
     }
     if (!DET) {
