@@ -45,10 +45,11 @@ RENDER_FWD_BYTES_PER_PAIR = 4 + 8 + 48          # list index, pixel box, the 48 
 RENDER_FWD_BYTES_PER_PIXEL = 12 + 4 + 4 + 4 + 4 + 4 + 1  # colour, depth, imax, T, last, count, hit
 RENDER_BWD_BYTES_PER_PAIR = 4 + 8 + 64 + 1      # list index, box, full record, active flag
 RENDER_BWD_BYTES_PER_PIXEL = 12 + 4 + 4         # dL/dC, T, last
-BIN_PARTS = {"count": ["k_count_reduce", "k_count_down"],
-             "sort": ["k_emit", "k_rt_up", "k_rt_scan", "k_os_hist", "k_os_scan", "k_os_pass", "k_ranges",
-                      "k_tile_order", "k_order_hist", "k_order_scan", "k_order_scatter"]}
-STAGE_KERNELS = {"project": ["k_project"], "bin": BIN_PARTS["count"] + BIN_PARTS["sort"],
+BIN_PARTS = {"count": ["k_tile_start", "k_tile_count", "k_tile_scan", "k_tile_offsets", "k_count_reduce",
+                       "k_count_down"],
+             "sort": ["k_tile_place", "k_tile_sort", "k_tile_sort_long", "k_emit", "k_rt_up", "k_rt_scan",
+                      "k_os_hist", "k_os_scan", "k_os_pass", "k_ranges", "k_tile_order", "k_order_hist", "k_order_scan", "k_order_scatter"]}
+STAGE_KERNELS = {"project": ["k_project", "k_project_views"], "bin": BIN_PARTS["count"] + BIN_PARTS["sort"],
                  "render_fwd": ["k_render_fwd"], "loss": ["k_l1_loss_grad"], "render_bwd": ["k_render_bwd"],
                  "project_bwd": ["k_project_bwd1", "k_project_bwd"]}
 
@@ -842,13 +843,11 @@ def main():
     n_act = int(step.active.sum().item()) if step.active is not None else n
     ev_fwd, ev_bwd = pair_evaluations(step)
     ni, nrec, tiles = int(st.n_isect), n * len(wl.cameras), int(st.tiles_total)
-    passes = (int(st.key_bits) + 7) // 8
-    ibits = max(1, (nrec - 1).bit_length())
-    pair_pass = 16 if int(st.key_bits) + ibits <= 64 else 24
     # algorithmic bytes per step of each stage (the per-unit figures above times the units)
     alg = {
         "project": n_vis * PROJECT_BYTES_PER_RECORD + (n - n_vis) * PROJECT_BYTES_PER_UNDRAWN,
-        "bin": nrec * 20 + (nrec * 20 + ni * 8 + ni * 8 + passes * pair_pass * ni + ni * 12 + tiles * 20),
+        # by tile: box and count read twice, offset written; a pair written, read and its index written
+        "bin": nrec * (16 + 16 + 4) + ni * (8 + 8 + 4) + tiles * 20,
         "render_fwd": ni * RENDER_FWD_BYTES_PER_PAIR + P * RENDER_FWD_BYTES_PER_PIXEL,
         "loss": P * 3 * 12,
         "render_bwd": ni * RENDER_BWD_BYTES_PER_PAIR + P * RENDER_BWD_BYTES_PER_PIXEL + ni * act_frac * 36,
