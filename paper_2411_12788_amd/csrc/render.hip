@@ -572,7 +572,9 @@ __device__ __forceinline__ void set_wave_priority(uint32_t list_len) {
 // LDS and 72 registers instead of 79 (seven waves per SIMD without
 // accumulation): 3M Gaussians at 1920x1080 with accumulation 599 -> 549 us and
 // without 340 -> 333 us, 100k at 637x479 with accumulation 126 -> 64 us, 4 views
-// of 1.5M 745 -> 707 us.
+// of 1.5M 745 -> 707 us.  With the walk's decisions as wave masks (62 vector
+// instructions per two entries instead of 78) the last 64 -> 61 and 712 -> 642 us,
+// 3M without accumulation 333 -> 305 us, 16 views of 1M 2517 -> 2279 us.
 template <bool ACC, bool OUT, int DEPTH>
 __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
                                                        const uint32_t* __restrict__ vals,
@@ -770,19 +772,22 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
       // of the loop latency.  The offsets of the next iteration are read ahead.
       const int group = (fresh((int)threadIdx.x) & 63) >> 4;
       int mine = group == 0 ? n4[0] : group == 1 ? n4[1] : group == 2 ? n4[2] : n4[3];
-      const int longest = rp ? 0 : max4(n4);
-      const uint32_t* sp = reinterpret_cast<const uint32_t*>(&s_stream[wv][group][0]);
-      uint32_t pair = *sp;
+      // What decides (which lanes pass, stop, are done) is kept as wave masks in
+      // scalar registers: only the comparisons are vector instructions.
+      const int longest = (int)uniform_u32((uint32_t)(rp ? 0 : max4(n4)));
+      const uint16_t* stream = &s_stream[wv][group][0];
+      uint32_t pair = *reinterpret_cast<const uint32_t*>(stream);
+      uint64_t stopped = __builtin_amdgcn_ballot_w64(done);
       for (int i = 0; i < longest; i += kFwdUnroll) {
         uint32_t off[kFwdUnroll];
-        bool has[kFwdUnroll];
+        uint64_t has[kFwdUnroll];
 #pragma unroll
         for (int u = 0; u < kFwdUnroll; ++u) {
-          has[u] = i + u < mine;
+          has[u] = __builtin_amdgcn_ballot_w64(i + u < mine);
           off[u] = (pair >> (16 * u)) & 0xffffu;
         }
-        sp += i + kFwdUnroll < kFwdBatch ? 1 : 0;
-        pair = *sp;
+        const int next = i + kFwdUnroll < kFwdBatch ? i + kFwdUnroll : i;
+        pair = *reinterpret_cast<const uint32_t*>(stream + next);
         float4 q2[kFwdUnroll];
         float al[kFwdUnroll], ee[kFwdUnroll], wg[kFwdUnroll];
 #pragma unroll
@@ -793,16 +798,21 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
           ee[u] = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
           al[u] = fminf(op.alpha_max, __builtin_amdgcn_exp2f(ee[u]));
         }
+        // (the index is read with the colour, not again where the weight is the largest)
+#pragma unroll
+        for (int u = 0; u < kFwdUnroll; ++u) asm("" : "+v"(q2[u].w));
+        uint64_t stops = 0;
 #pragma unroll
         for (int u = 0; u < kFwdUnroll; ++u) {
           // Branch-free per lane: selects keep the state of lanes that skip the
           // entry or have stopped (staged records are finite, so adding a zero
           // weight leaves the colour unchanged).
-          const bool pass = has[u] && !done && ee[u] >= op.log2_alpha_min;
+          const uint64_t pass = has[u] & ~stopped & __builtin_amdgcn_ballot_w64(ee[u] >= op.log2_alpha_min);
           const float Tn = T * (1.f - al[u]);
-          const bool stop = pass && Tn < op.t_min;
-          const bool inc = pass && !stop;
-          done = done || stop;
+          const uint64_t stop = pass & __builtin_amdgcn_ballot_w64(Tn < op.t_min);
+          const bool inc = __builtin_amdgcn_inverse_ballot_w64(pass & ~stop);
+          stopped |= stop;
+          stops |= stop;
           const float wgt = inc ? al[u] * T : 0.f;
           T = inc ? Tn : T;
           c0 += wgt * q2[u].x;
@@ -824,11 +834,13 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
             atomicMax(&s_acc_m[k], __float_as_uint(r.max));  // weights are >= 0: bit patterns have their order
           }
         }
-        // a group whose pixels have all stopped drops the rest of its stream
-        const uint64_t dm = __builtin_amdgcn_ballot_w64(done);
-        if (((dm >> (16 * group)) & 0xffffull) == 0xffffull) mine = 0;
-        if (dm == ~0ull) break;
+        if (stops != 0) {
+          // a group whose pixels have all stopped drops the rest of its stream
+          if (stopped == ~0ull) break;
+          if (((stopped >> (16 * group)) & 0xffffull) == 0xffffull) mine = 0;
+        }
       }
+      done = __builtin_amdgcn_inverse_ballot_w64(stopped);
     }
     if (!rp && at != kNoOffset) lastpos = base - start + (at >> 4) + 1;
     if (ACC) {
@@ -1213,7 +1225,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       // One entry of the group's stream per iteration, latest first; the
       // transmittance is restored through them in reverse order.
       const int mine = grp == 0 ? n4[0] : grp == 1 ? n4[1] : grp == 2 ? n4[2] : n4[3];
-      const int longest = rp ? 0 : max4(n4);
+      const int longest = (int)uniform_u32((uint32_t)(rp ? 0 : max4(n4)));
       const uint8_t* sp = &s_stream[wv][grp][0] + (mine > 0 ? mine - 1 : 0);
       uint32_t ahead = *sp;
       for (int i = 0; i < longest; ++i) {
