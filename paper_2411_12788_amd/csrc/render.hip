@@ -675,17 +675,21 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
       // not depend on how many entries a round has.  Two fours per iteration:
       // their records are read and their alphas and products formed side by
       // side, then they are composited in order.
+      // What decides (which lanes pass, stop, are done) is kept as wave masks in
+      // scalar registers: only the comparisons are vector instructions.
+      uint64_t stopped = __builtin_amdgcn_ballot_w64(done);
       uint64_t met = am;  // pixels that the rest of the stream was tested against
 #pragma unroll 1
       for (int i = 0; rp && i < n4[3];) {
         const int row = (fresh((int)threadIdx.x) & 63) >> 4;
-        const uint64_t now = __builtin_amdgcn_ballot_w64(!done);
+        const uint64_t now = ~stopped;
         if (now == 0) break;
         if (now != met) {  // rare: some pixel has stopped in the chunk that ended here
           for (int from = i; from < n4[3];) {
             const int end = from < n4[1] ? n4[1] : from < n4[2] ? n4[2] : n4[3];
-            retest_chunk(s_stream[wv][0], from, end, s_r0, s_r1, s_r2, bin, (uint32_t)now & 0xffffu, fresh_uniform(ix0), fresh_uniform(iy0),
-                         (wv & 1) * 4, (wv >> 1) * 4, fresh(lane), op.log2_alpha_min);
+            retest_chunk(s_stream[wv][0], from, end, s_r0, s_r1, s_r2, bin, (uint32_t)now & 0xffffu,
+                         fresh_uniform(ix0), fresh_uniform(iy0), (wv & 1) * 4, (wv >> 1) * 4, fresh(lane),
+                         op.log2_alpha_min);
             from = end;
           }
           met = now;
@@ -695,7 +699,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
 #pragma unroll 1
         for (; i < until; i += 2 * kGroups, sp += 2 * kGroups) {
           uint32_t off[2];
-          bool pass[2];
+          uint64_t pass[2];
           float4 q2[2];
           float al[2], om[2], wg[2];
           RowScan tf[2];
@@ -709,15 +713,17 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
             const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
             const float ee = r1.w - (r1.x * dx * dx + r1.y * dx * dy + r1.z * dy * dy);
             al[u] = fminf(op.alpha_max, __builtin_amdgcn_exp2f(ee));
-            pass[u] = hr && !done && ee >= op.log2_alpha_min;
-            om[u] = pass[u] ? 1.f - al[u] : 1.f;
+            pass[u] = __builtin_amdgcn_ballot_w64(entry != kNoEntry) & ~stopped &
+                      __builtin_amdgcn_ballot_w64(ee >= op.log2_alpha_min);
+            om[u] = __builtin_amdgcn_inverse_ballot_w64(pass[u]) ? 1.f - al[u] : 1.f;
             tf[u] = rows_scan_mul(om[u], row);
           }
 #pragma unroll
+          for (int u = 0; u < 2; ++u) asm("" : "+v"(q2[u].w));
+#pragma unroll
           for (int u = 0; u < 2; ++u) {
-            const bool stop = pass[u] && T * tf[u].incl < op.t_min;
-            const uint64_t sb = __builtin_amdgcn_ballot_w64(stop);
-            bool inc = pass[u];
+            const uint64_t sb = pass[u] & __builtin_amdgcn_ballot_w64(T * tf[u].incl < op.t_min);
+            uint64_t in = pass[u];
             float Tn = T * tf[u].total;
             if (sb != 0ull) {
               // rare: some pixel stops at one of these entries; later rows of its
@@ -726,19 +732,21 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
               const int l = fresh(lane);
               const uint64_t col = 0x0001000100010001ull << (l & 15);
               const bool earlier = (sb & col & ((1ull << (l & 48)) - 1ull)) != 0;
-              inc = pass[u] && !stop && !earlier;
-              Tn = T * rows_scan_mul(inc ? om[u] : 1.f, row).total;
-              done = done || (sb & col) != 0;
+              in = pass[u] & ~sb & ~__builtin_amdgcn_ballot_w64(earlier);
+              Tn = T * rows_scan_mul(__builtin_amdgcn_inverse_ballot_w64(in) ? om[u] : 1.f, row).total;
+              const uint64_t columns = (sb | (sb >> 16) | (sb >> 32) | (sb >> 48)) & 0xffffull;
+              stopped |= columns * 0x0001000100010001ull;
               // the walk leaves off at the end of this chunk, which may be
               // between the two fours (row 0 of a four always has an entry)
               const uint32_t chunk = uniform_u32(off[u]) / (16u * kWave);
               until = chunk == 0 ? n4[0] : chunk == 1 ? n4[1] : chunk == 2 ? n4[2] : n4[3];
               if (u == 0) {
-                pass[1] = pass[1] && !done && i + kGroups < until;
-                om[1] = pass[1] ? om[1] : 1.f;
+                pass[1] = i + kGroups < until ? pass[1] & ~stopped : 0ull;
+                om[1] = __builtin_amdgcn_inverse_ballot_w64(pass[1]) ? om[1] : 1.f;
                 tf[1] = rows_scan_mul(om[1], row);
               }
             }
+            const bool inc = __builtin_amdgcn_inverse_ballot_w64(in);
             const float wgt = inc ? al[u] * (T * tf[u].excl) : 0.f;
             c0 += wgt * q2[u].x;
             c1 += wgt * q2[u].y;
@@ -772,12 +780,9 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
       // of the loop latency.  The offsets of the next iteration are read ahead.
       const int group = (fresh((int)threadIdx.x) & 63) >> 4;
       int mine = group == 0 ? n4[0] : group == 1 ? n4[1] : group == 2 ? n4[2] : n4[3];
-      // What decides (which lanes pass, stop, are done) is kept as wave masks in
-      // scalar registers: only the comparisons are vector instructions.
       const int longest = (int)uniform_u32((uint32_t)(rp ? 0 : max4(n4)));
       const uint16_t* stream = &s_stream[wv][group][0];
       uint32_t pair = *reinterpret_cast<const uint32_t*>(stream);
-      uint64_t stopped = __builtin_amdgcn_ballot_w64(done);
       for (int i = 0; i < longest; i += kFwdUnroll) {
         uint32_t off[kFwdUnroll];
         uint64_t has[kFwdUnroll];
