@@ -326,7 +326,7 @@ def bin(proj: Projected, cams, n: int, want_keys: bool = False, stream=None, che
     status flag is read back (one synchronisation) where it can be raised: by
     the look-back sort, whose workgroups wait for each other.  The default
     sort and the lists made by tile wait on nobody, and nothing is read back
-    (33 us of a training step of 4k Gaussians, twice).  With an explicit
+    (55 us of the forward of a step of 4k Gaussians before).  With an explicit
     `stream` it always is: the workspaces belong to the current stream and may
     be reused there once this returns."""
     buffers = StepBuffers()
