@@ -311,25 +311,27 @@ constexpr int kBwdBatch = MASKED || DET ? 256 : 192;
 // the four groups four times as often.
 constexpr int kGroups = 4;
 constexpr int kWaves = kBlock / kWave;
-template <int BATCH>
+// The backward knows in which chunks a pixel still composites (PER_CHUNK), the
+// forward only whether it does at the start of the round.
+template <int BATCH, bool PER_CHUNK>
 struct RoundLds {
   static constexpr int chunks = BATCH / kWave;
-  uint64_t active[kWaves];                  // pixels of each wave that still composite
+  uint64_t active[kWaves][PER_CHUNK ? chunks : 1];  // pixels of each wave that still composite
   uint64_t mask[kWaves][kGroups][chunks];
   __device__ __forceinline__ bool none_active() const {
     uint64_t any = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) any |= active[w];
+    for (int w = 0; w < kWaves; ++w) any |= active[w][0];
     return uniform_u64(any) == 0;
   }
 };
 // `group_last` (or NULL): list positions from which on a group composites nothing.
 // Returns the entries of this wave's chunk that some group walks.
-template <int BATCH>
-__device__ __forceinline__ uint64_t test_round(RoundLds<BATCH>& s, const uint32_t* group_last, uint32_t pos, bool split,
+template <int BATCH, bool PER_CHUNK>
+__device__ __forceinline__ uint64_t test_round(RoundLds<BATCH, PER_CHUNK>& s, const uint32_t* group_last, uint32_t pos, bool split,
                                                int32_t ix0, int32_t iy0, int2 box, float4 r0, float4 r1, bool in,
                                                int wv, int lane, float log2_alpha_min) {
-  if (wv >= RoundLds<BATCH>::chunks) return 0;
+  if (wv >= RoundLds<BATCH, PER_CHUNK>::chunks) return 0;
   uint64_t any = 0;
   uint32_t lo = 0, hi = 0;  // lane 4 w + g keeps the mask of group g of wave w
   if (__builtin_amdgcn_ballot_w64(in) != 0) {
@@ -338,7 +340,7 @@ __device__ __forceinline__ uint64_t test_round(RoundLds<BATCH>& s, const uint32_
     if (group_last) last = group_last[lane & (kWaves * kGroups - 1)];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const uint64_t am = uniform_u64(s.active[w]);
+      const uint64_t am = uniform_u64(s.active[w][PER_CHUNK ? wv : 0]);
 #pragma unroll
       for (int g = 0; g < kGroups; ++g) {
         const uint32_t two = (uint32_t)(g < 2 ? am : am >> 32);
@@ -365,18 +367,18 @@ __device__ __forceinline__ uint64_t test_round(RoundLds<BATCH>& s, const uint32_
 }
 // Entries of this wave's groups, `unit` per staged entry; n[g]: their counts.
 // By chunk, in a split work item: n[c] is where chunk c's part of the one
-// group's stream ends, filled up with kNoEntry to a multiple of four.
+// group's stream ends (FILL: filled up with kNoEntry to a multiple of four).
 constexpr uint16_t kNoEntry = 0xffff;
 __device__ __forceinline__ int fill_four(uint16_t* stream, int n, int lane) {
   const int fill = -n & 3;
   if (lane < fill) stream[n + lane] = kNoEntry;
   return n + fill;
 }
-template <bool BY_CHUNK, typename T, int BATCH>
-__device__ __forceinline__ void make_streams(const RoundLds<BATCH>& s, T (*stream)[BATCH], int unit, bool split,
-                                             bool by_chunk, int wv, int lane, int (&n)[kGroups]) {
-  constexpr int kChunks = RoundLds<BATCH>::chunks;
-  static_assert(!BY_CHUNK || kChunks == kGroups, "n holds one end per chunk");
+template <bool FILL, typename T, int BATCH, bool PER_CHUNK>
+__device__ __forceinline__ void make_streams(const RoundLds<BATCH, PER_CHUNK>& s, T (*stream)[BATCH], int unit,
+                                             bool split, bool by_chunk, int wv, int lane, int (&n)[kGroups]) {
+  constexpr int kChunks = RoundLds<BATCH, PER_CHUNK>::chunks;
+  static_assert(kChunks <= kGroups, "n holds one end per chunk");
   const uint64_t mine = (&s.mask[wv][0][0])[lane < kGroups * kChunks ? lane : 0];
   auto put = [&](int g, int c, int at) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, g * kChunks + c);
@@ -387,16 +389,17 @@ __device__ __forceinline__ void make_streams(const RoundLds<BATCH>& s, T (*strea
           (T)((c * kWave + lane) * unit);
     return (int)__popcll(m);
   };
-  bool grouped = true;
-  if constexpr (BY_CHUNK) {
-    if (by_chunk) {
-      grouped = false;
-      int at = 0;
+  if (by_chunk) {
+    int at = 0;
 #pragma unroll
-      for (int c = 0; c < kChunks; ++c) n[c] = at = fill_four(stream[0], at + put(0, c, at), lane);
+    for (int c = 0; c < kGroups; ++c) {
+      if (c < kChunks) {
+        at += put(0, c, at);
+        if constexpr (FILL) at = fill_four(stream[0], at, lane);
+      }
+      n[c] = at;
     }
-  }
-  if (grouped) {
+  } else {
 #pragma unroll
     for (int g = 0; g < kGroups; ++g) {
       n[g] = 0;
@@ -587,7 +590,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   // s_r2[k].w carries the record index (the forward never reads the opacity
   // field), so one read returns colour and index
   __shared__ float4 s_r0[kFwdBatch], s_r1[kFwdBatch], s_r2[kFwdBatch];
-  __shared__ RoundLds<kFwdBatch> s_round;
+  __shared__ RoundLds<kFwdBatch, false> s_round;
   __shared__ float s_z[DEPTH == GS_DEPTH_BLEND ? kFwdBatch : 1];
   // per staged entry: importance and max weight gathered from the whole
   // workgroup with LDS atomics, flushed with one global atomic per entry
@@ -639,7 +642,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   for (uint32_t base = start; base < end; base += kFwdBatch) {
     const uint32_t tid = (uint32_t)fresh((int)threadIdx.x);
     const uint64_t am = __builtin_amdgcn_ballot_w64(!done);
-    if (lane == 0) s_round.active[wv] = am;
+    if (lane == 0) s_round.active[wv][0] = am;
     __syncthreads();  // also orders this round's LDS writes after the last round's reads
     if (s_round.none_active()) break;
     const uint32_t count = (end - base) < (uint32_t)kFwdBatch ? (end - base) : (uint32_t)kFwdBatch;
@@ -945,19 +948,24 @@ __device__ __forceinline__ StagedB fetch_entry_bwd(const float* __restrict__ rec
 // The nine sums of an entry over each 16-lane row (4x4 pixels): of six per-lane
 // partials p, and of the weight w times the three channels of dL/dcolour.
 //
-// Partials: each step adds the other half of the lanes and keeps one value in
-// either half: lanes 8 apart (a row rotate; values 2 j and 2 j + 1 share a
-// register), then the two quads of a half row (its mirror), then the lanes of a
-// quad.  The halves are chosen by the bank mask of the add itself (lanes of a
-// disabled bank keep the register's value), so a pair of values costs two
-// instructions and no selects, which the compiler cannot express: hence the
-// assembly.  Channels: lane m of a quad sums channel m over the quad's pixels,
-// w of each pixel by a broadcast inside the quad times that pixel's channel m
-// (gm, the same for all entries), then the four quads are added: six
-// instructions instead of three products and ten.  A DPP read needs two
-// instructions after the write of its register; the order below keeps that
-// distance.  Returned: in lane L of a row the total of value sum_slot(L), where
-// that is not negative.
+// Partials: the four lanes of a quad (lane xor 1, then xor 2), then lanes 8
+// apart (a row rotate), then the two quads of a half row (its mirror: the lanes
+// of a quad hold the same value by then).  The last two steps keep one value in
+// either half (values 2 j and 2 j + 1 share a register), chosen by the bank mask
+// of the add itself (lanes of a disabled bank keep the register's value), so a
+// pair of values costs two instructions and no selects, which the compiler
+// cannot express: hence the assembly.  Starting with the halves takes 13
+// instructions instead of 21 and was not kept: the gradient of a needle's scales
+// is a difference of the second moments smaller than they are by the square of
+// its elongation, so it shows every rounding in which the three differ, and
+// another tree (with the scalar suffix, see alpha_gradient) moved it by three
+// times the noise of the atomics.  Channels: lane m of a quad sums
+// channel m over the quad's pixels, w of each pixel by a broadcast inside the
+// quad times that pixel's channel m (gm, the same for all entries), then the
+// four quads are added: six instructions instead of three products and ten.  A
+// DPP read needs two instructions after the write of its register; the order
+// below keeps that distance.  Returned: in lane L of a row the total of value
+// sum_slot(L), where that is not negative.
 __device__ __forceinline__ int sum_slot(int lane) {
   const int q = (lane >> 2) & 3, r = lane & 3;
   if (r == 3) return 2 * (q & 1) + (q >> 1);  // quads hold values 0, 2, 1, 3
@@ -983,50 +991,70 @@ __device__ __forceinline__ ChannelPixels channel_pixels(float g0, float g1, floa
   return r;
 }
 __device__ __forceinline__ float row_sum9(const float (&p)[6], float w, const ChannelPixels& gm, int lane) {
-  float a, b, c, d, f, h;
+  float q0 = p[0], q1 = p[1], q2 = p[2], q3 = p[3], q4 = p[4], q5 = p[5], a, b, c, d, f, h;
   asm("s_nop 1\n\t"
       "v_mul_f32_dpp %5, %12, %13 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %7, %7, %7 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %8, %8, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %9, %9, %9 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %10, %10, %10 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %11, %11, %11 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, %12, %14 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %7, %7, %7 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %8, %8, %8 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %9, %9, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %10, %10, %10 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %11, %11, %11 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %5, %12, %15 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %0, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
       "v_add_f32_dpp %1, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
       "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_fmac_f32_dpp %5, %12, %16 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %0, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
       "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
       "v_add_f32_dpp %2, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_fmac_f32_dpp %5, %12, %14 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %3, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_fmac_f32_dpp %5, %12, %15 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %3, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
       "v_add_f32_dpp %4, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %5, %12, %16 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %3, %3, %3 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %5, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %3, %3, %3 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
       "v_add_f32_dpp %5, %5, %5 row_ror:4 row_mask:0xf bank_mask:0xf"
-      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d), "=&v"(f), "=&v"(h)
-      : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(w), "v"(gm.x[0]), "v"(gm.x[1]),
-        "v"(gm.x[2]), "v"(gm.x[3]));
+      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d), "=&v"(f), "=&v"(h), "+v"(q0), "+v"(q1), "+v"(q2), "+v"(q3), "+v"(q4),
+        "+v"(q5)
+      : "v"(w), "v"(gm.x[0]), "v"(gm.x[1]), "v"(gm.x[2]), "v"(gm.x[3]));
   return (lane & 3) == 3 ? d : (lane & 12) == 0 ? h : f;
+}
+
+// dL/dalpha of one entry of a pixel, with the transmittance T in front of it,
+// 1 / (1 - alpha) and the colour composited behind it, channel by channel.  The
+// suffix as one scalar (its product with dL/dcolour) saves six instructions and,
+// in split work items, two of the three scans; not kept for the reason row_sum9
+// gives (it also turns an infinite dL/dcolour times a zero background into NaN).
+__device__ __forceinline__ float alpha_gradient(const float (&g)[3], float4 c, float T, float iom, const float (&s)[3]) {
+  const float x0 = __builtin_fmaf(c.x, T, -(s[0] * iom));
+  const float x1 = __builtin_fmaf(c.y, T, -(s[1] * iom));
+  const float x2 = __builtin_fmaf(c.z, T, -(s[2] * iom));
+  return __builtin_fmaf(g[2], x2, __builtin_fmaf(g[0], x0, g[1] * x1));
 }
 
 // The nine sums of an entry over pixels, with e = dL/dalpha alpha (0 where
 // alpha is clamped or the entry is not composited) and w the weight:
-//   0, 1: sum e dx, e dy   2, 3, 4: sum e dx dx, e dx dy, e dy dy
+//   0, 1: sum e (2 A dx + B dy), e (B dx + 2 C dy)
+//   2, 3, 4: sum e dx dx, e dx dy, e dy dy
 //   5: sum e               6, 7, 8: sum w dL/dcolour
-// What the 2D gradient adds to them is constant per record (conic, opacity),
-// so it is applied once to the sums (g2d_component) instead of per pixel.
-//
-// Component c of the record's 2D gradient from its sums: dL/du = a S0 + b S1,
-// dL/dv = b S0 + c S1 with the conic (a, b, c) = (2 A, B, 2 C) / log2(e) of the
-// staged (A, B, C); dL/d(conic) = (-S2 / 2, -S3, -S4 / 2); dL/d(opacity) =
-// S5 / opacity; the colour sums as they are.
-// x = Sc, and y the other of S0 and S1 for c < 2.
-__device__ __forceinline__ float g2d_component(int c, float x, float y, float A, float B, float C, float opacity) {
+// with the staged conic (A, B, C), log2(e) / 2 times the conic with B twice its
+// off-diagonal.  What else the 2D gradient adds to them is constant per record,
+// so it is applied once to the sums: the record's gradient is (ln 2 S0, ln 2 S1,
+// -S2 / 2, -S3, -S4 / 2, S5 / opacity, S6, S7, S8).  The conic stays inside the
+// first two: for a needle 2 A dx + B dy cancels by its elongation, and taken of
+// the sums instead of per pixel it magnified their rounding (error of the means
+// against 64 bits 4 to 7 % larger at elongations of 10 to 32; five vector
+// instructions per walked entry).
+__device__ __forceinline__ float g2d_component(int c, float x, float opacity) {
   constexpr float kLn2 = 0.6931471805599453f;
-  const float pair = kLn2 * (2.f * (c == 0 ? A : C) * x + B * y);
-  const float scale = c == 5 ? __builtin_amdgcn_rcpf(opacity) : c > 5 ? 1.f : c == 3 ? -1.f : -0.5f;
-  return c < 2 ? pair : scale * x;
+  const float scale = c < 2 ? kLn2 : c == 5 ? __builtin_amdgcn_rcpf(opacity) : c > 5 ? 1.f : c == 3 ? -1.f : -0.5f;
+  return scale * x;
 }
 
 // One group's sums of one entry leave the row from nine of its lanes: into the
@@ -1059,8 +1087,7 @@ __device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ par
 // entries back to front from the largest `last` of the workgroup.  Per pixel:
 // restore the transmittance in front of the Gaussian (T /= 1 - alpha), form
 // dL/dalpha from the colour composited behind it, and add the Gaussian's own
-// weighted colour to that suffix.  Only the products of the colours with
-// dL/dcolour enter dL/dalpha, so the suffix is that one scalar.  Entries of
+// weighted colour to that suffix.  Entries of
 // inactive Gaussians update the per-pixel state but emit no gradient.  The
 // nine sums of a group's entry are formed over its 16 lanes in registers and
 // added by nine of its lanes to the entry's accumulators in LDS; after each
@@ -1069,11 +1096,12 @@ __device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ par
 // (entry, group): float atomics are carried out at the memory side (at most
 // ~17 G requests/s), which bounded the kernel where most entries are active
 // (1M Gaussians, 16 views, 17.3M pixels, all active: 169M -> 31M requests).
-// Now bound by the vector instructions of the walk.  Measured there: with
-// those sums, list streams and the scalar suffix 9.76 -> 6.42 ms; with the
-// tests in the staging thread 5.80 ms; with double accumulators 4.34 ms; with
-// the channel sums and tests of row_sum9 and emit_partial (64 vector
-// instructions per walked entry instead of 80) 4.08 ms.
+// Now bound by the vector instructions of the walk.  Measured there, against
+// partials summed straight into the 2D gradients: 9.31 -> 4.33 ms; 500k
+// Gaussians at 1245x825 395 -> 298 us, 3M at 1920x1080 with a quarter of them
+// active 628 -> 556 us.  What sums and suffix would save and the gradients of
+// needles do not allow (row_sum9, alpha_gradient, the conic of g2d_component):
+// 3.69 ms, 225 us, 490 us.
 template <bool MASKED, bool DET>
 __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
                                                        const uint32_t* __restrict__ vals,
@@ -1088,7 +1116,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   constexpr int kBatch = kBwdBatch<MASKED, DET>;
   using Acc = std::conditional_t<MASKED, float, double>;
   __shared__ float4 s_r0[kBatch], s_r1[kBatch], s_r2[kBatch];
-  __shared__ RoundLds<kBatch> s_round;
+  __shared__ RoundLds<kBatch, true> s_round;
   // the staged entries' sums over the workgroup; all zero at the start of a round
   __shared__ Acc s_acc[DET ? 1 : kBatch * kG2d];
   __shared__ uint8_t s_stream[kWaves][kGroups][kBatch];
@@ -1120,19 +1148,17 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   set_wave_priority(end - start);
   const int64_t P = vs.pixels_total;
   const int64_t gp = cam.pixel_base + (int64_t)py * cam.width + px;
-  float T = 1.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
+  float T = 1.f, g[3] = {0.f, 0.f, 0.f};
   uint32_t lst = 0;
   if (inside) {
     T = t_final[gp];
     lst = last[gp];
-    g0 = dldc[gp];
-    g1 = dldc[P + gp];
-    g2 = dldc[2 * P + gp];
+    for (int k = 0; k < 3; ++k) g[k] = dldc[k * P + gp];
   }
   lst = lst < end - start ? lst : end - start;  // `last` never exceeds the tile's list
-  float S = T * (g0 * op.bg[0] + g1 * op.bg[1] + g2 * op.bg[2]);  // dL/dcolour . colour composited behind
+  float S[3] = {T * op.bg[0], T * op.bg[1], T * op.bg[2]};  // colour composited behind
   const int slot = sum_slot(lane);  // the sum this lane emits after row_sum9, or -1
-  const ChannelPixels gm = channel_pixels(g0, g1, g2, lane);
+  const ChannelPixels gm = channel_pixels(g[0], g[1], g[2], lane);
   {
     uint32_t m = lst;  // over the 16 lanes of a group; split rows hold the same pixels
 #pragma unroll
@@ -1151,7 +1177,19 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   // Rounds cover [base, top) downwards from start + bjmax.  Staging pipeline:
   // the records of the next round and the list indices of the one after are
   // in flight while a round is processed.
-  auto round_base = [&](uint32_t top) { return top - start > (uint32_t)kBatch ? top - kBatch : start; };
+  // In a split work item which entries share a product of transmittances, and
+  // with it the rounding, must not depend on the rounds' length: fours are of one
+  // chunk of 64, and the chunks are those of rounds of 256 (the last `tail`
+  // entries counted from the start, the others from the end).
+  const uint32_t tail = bjmax > 0u ? ((bjmax - 1u) & 255u) + 1u : 0u;
+  auto round_base = [&](uint32_t top) {
+    const uint32_t r = top - start;
+    if (kBatch < 256 && rp) {
+      if (r > tail) return r - tail > (uint32_t)kBatch ? top - kBatch : start + tail;
+      return r > (uint32_t)kBatch ? start + kBatch : start;
+    }
+    return r > (uint32_t)kBatch ? top - kBatch : start;
+  };
   uint32_t top = start + bjmax;
   uint32_t base = round_base(top);
   const uint32_t mine_at = threadIdx.x;
@@ -1162,9 +1200,13 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   uint32_t nidx = stager && nbase + mine_at < ntop ? vals[nbase + mine_at] : 0u;
   while (top > start) {
     const uint32_t count = top - base;
-    // pixels whose last entry lies above the round's first
+    // pixels whose last entry lies above the round's, and each chunk's, first
     const uint64_t am = __builtin_amdgcn_ballot_w64(lst > base - start);
-    if (lane == 0) s_round.active[wv] = am;
+#pragma unroll
+    for (int c = 0; c < kBatch / kWave; ++c) {
+      const uint64_t in = c == 0 ? am : __builtin_amdgcn_ballot_w64(lst > base - start + c * kWave);
+      if (lane == 0) s_round.active[wv][c] = in;
+    }
     __syncthreads();  // the previous round's entries are consumed
     if (stager) {
       s_r0[mine_at] = cur.r0;
@@ -1184,7 +1226,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
     }
     if (am != 0) {
       int n4[kGroups];
-      make_streams<false>(s_round, s_stream[wv], 1, rp, false, wv, fresh(lane), n4);
+      make_streams<false>(s_round, s_stream[wv], 1, rp, rp, wv, fresh(lane), n4);
       // round-relative offset from which on the pixel composited nothing
       const uint32_t lim = lst > base - start ? (lst - (base - start)) * 16u : 0u;
       // Split work item: row r takes the r-th latest of the next four entries
@@ -1192,10 +1234,16 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       // product of 1 / (1 - alpha) over the rows up to it, its suffix colour
       // the sum of the weighted colours of the rows before it; the nine
       // partials of each row's entry are then summed over the row as usual.
-      int left = rp ? n4[0] : 0;
-      for (const uint8_t* sp = &s_stream[wv][0][0] + left - 1 - grp; left > 0; left -= kGroups, sp -= kGroups) {
-        const bool hr = grp < left;
-        const uint32_t off = hr ? (uint32_t)*sp * 16u : 0u;
+      int left = rp ? n4[kBatch / kWave - 1] : 0;
+      auto chunk_first = [&](int at) { return at > n4[2] ? n4[2] : at > n4[1] ? n4[1] : at > n4[0] ? n4[0] : 0; };
+      int floor = chunk_first(left);
+      uint32_t offn = s_stream[wv][0][left - floor > grp ? left - 1 - grp : floor];
+      while (left > 0) {
+        const bool hr = left - floor > grp;
+        const uint32_t off = offn * 16u;
+        left = left - floor > kGroups ? left - kGroups : floor;
+        floor = chunk_first(left);
+        offn = s_stream[wv][0][left - floor > grp ? left - 1 - grp : floor];
         const bool val = hr && off < lim;
         const float4 r0 = lds_at(s_r0, off), r1 = lds_at(s_r1, off), c4 = lds_at(s_r2, off);
         const float dx = (pxc - r0.x) - r0.z, dy = (pyc - r0.y) - r0.w;
@@ -1208,20 +1256,24 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const RowScan tr = rows_scan_mul(inc ? iom : 1.f, grp);
         const float Tr = T * tr.incl;
         const float wgt = inc ? al * Tr : 0.f;
-        const float cg = g0 * c4.x + g1 * c4.y + g2 * c4.z;
-        const RowScan us = rows_scan_add(wgt * cg, grp);
-        const float ga = Tr * cg - (S + us.excl) * iom;
+        const RowScan u0 = rows_scan_add(wgt * c4.x, grp), u1 = rows_scan_add(wgt * c4.y, grp),
+                      u2 = rows_scan_add(wgt * c4.z, grp);
+        const float Sr[3] = {S[0] + u0.excl, S[1] + u1.excl, S[2] + u2.excl};
+        const float ga = alpha_gradient(g, c4, Tr, iom, Sr);
         float pv[6];
         const float wa = !MASKED || act ? wgt : 0.f;
         const float gal = (act && G2 < op.alpha_max) ? ga * al : 0.f;
         pv[5] = gal;
-        pv[0] = gal * dx;
-        pv[1] = gal * dy;
-        pv[2] = pv[0] * dx;
-        pv[3] = pv[0] * dy;
-        pv[4] = pv[1] * dy;
+        const float gx = gal * dx, gy = gal * dy;
+        pv[0] = gal * __builtin_fmaf(2.f, r1.x * dx, r1.y * dy);
+        pv[1] = gal * __builtin_fmaf(2.f, r1.z * dy, r1.y * dx);
+        pv[2] = gx * dx;
+        pv[3] = gx * dy;
+        pv[4] = gy * dy;
         T = T * tr.total;
-        S += us.total;
+        S[0] += u0.total;
+        S[1] += u1.total;
+        S[2] += u2.total;
         // (a weight is positive wherever the entry is composited)
         const uint64_t cm = __builtin_amdgcn_ballot_w64(wa > 0.f);
         if (cm != 0)
@@ -1252,9 +1304,10 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const float iom = __builtin_amdgcn_rcpf(1.f - al);
         T = inc ? T * iom : T;
         const float wgt = inc ? al * T : 0.f;
-        const float cg = g0 * c4.x + g1 * c4.y + g2 * c4.z;
-        const float ga = T * cg - S * iom;
-        S += wgt * cg;
+        const float ga = alpha_gradient(g, c4, T, iom, S);
+        S[0] = __builtin_fmaf(wgt, c4.x, S[0]);
+        S[1] = __builtin_fmaf(wgt, c4.y, S[1]);
+        S[2] = __builtin_fmaf(wgt, c4.z, S[2]);
         const float wa = !MASKED || act ? wgt : 0.f;
         const uint64_t cm = __builtin_amdgcn_ballot_w64(wa > 0.f);
         if (cm == 0) continue;
@@ -1262,11 +1315,12 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         // the clamped alpha has no gradient with respect to opacity or shape
         const float gal = (act && G2 < op.alpha_max) ? ga * al : 0.f;
         pv[5] = gal;
-        pv[0] = gal * dx;
-        pv[1] = gal * dy;
-        pv[2] = pv[0] * dx;
-        pv[3] = pv[0] * dy;
-        pv[4] = pv[1] * dy;
+        const float gx = gal * dx, gy = gal * dy;
+        pv[0] = gal * __builtin_fmaf(2.f, r1.x * dx, r1.y * dy);
+        pv[1] = gal * __builtin_fmaf(2.f, r1.z * dy, r1.y * dx);
+        pv[2] = gx * dx;
+        pv[3] = gx * dy;
+        pv[4] = gy * dy;
         emit_partial<DET>(s_acc, part, pmask, k, base, g16, slot, cm, grp, row_sum9(pv, wa, gm, lane));
       }
     }
@@ -1290,10 +1344,8 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const uint32_t k = list[e];
         const uint32_t r = vals[base + k];  // a walked entry's index is valid
         Acc* ap = s_acc + k * kG2d;
-        const float x = (float)ap[fc], y = (float)ap[fc ^ (fc < 2 ? 1 : 0)];
+        const float val = g2d_component(fc, (float)ap[fc], fabsf(s_r2[k].w));
         ap[fc] = Acc(0);
-        const float4 r1 = s_r1[k];
-        const float val = g2d_component(fc, x, y, r1.x, r1.y, r1.z, fabsf(s_r2[k].w));
         if (val != 0.f) atomicAdd(g2d + (int64_t)r * kG2d + fc, val);
       }
     }
@@ -1380,11 +1432,9 @@ __global__ __launch_bounds__(kBlock) void k_det_record(const int32_t* __restrict
 #pragma unroll
     for (int c = 0; c < kG2d; ++c) acc[c] += tpart[(e0 + k) * kG2d + c];
   }
-  const float4* R4 = reinterpret_cast<const float4*>(rec + r * kRecFloats);
-  const float4 r1 = R4[1];
-  const float op = R4[2].w;
+  const float op = rec[r * kRecFloats + 11];
 #pragma unroll
-  for (int c = 0; c < kG2d; ++c) g2d[r * kG2d + c] += g2d_component(c, acc[c], acc[c < 2 ? 1 - c : c], r1.x, r1.y, r1.z, op);
+  for (int c = 0; c < kG2d; ++c) g2d[r * kG2d + c] += g2d_component(c, acc[c], op);
 }
 
 size_t det_ws_bytes(int64_t n_isect) {
