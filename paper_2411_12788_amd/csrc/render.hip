@@ -203,9 +203,17 @@ __device__ __forceinline__ bool box_meets(int2 b, int32_t x0, int32_t x1, int32_
 
 // One list entry as staged in LDS: record index, pixel box, the first 48
 // bytes of its record (screen mean, scaled conic, colour and opacity) and,
-// for blended depth, its camera depth.  A corrupt index (>= V n) is replaced by
-// an entry with an empty box, so it is never dereferenced and never drawn.
+// for blended depth, its camera depth.  Where there is no entry (past the list's
+// end) or its index is corrupt (>= V n), the box is empty, so it is never drawn,
+// and colour and depth are staged as zeros: a group walks to the longest of its
+// wave's streams and multiplies what lies past its own by a weight of 0, which
+// has to be finite, and row 0, read in its place, need not be (the projection
+// leaves the rows of records that are not drawn unwritten).  The zeros are
+// chosen when the entry is staged, a round after its loads: with the loads under
+// the condition instead 3M Gaussians at 1920x1080 with accumulation took 603 us,
+// so 556 (the backward takes the same either way).
 struct Staged {
+  __device__ __forceinline__ bool entry() const { return box.x != 0xffff; }
   uint32_t idx;
   int2 box;
   float4 r0, r1, r2;
@@ -648,8 +656,10 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
     const uint32_t count = (end - base) < (uint32_t)kFwdBatch ? (end - base) : (uint32_t)kFwdBatch;
     s_r0[tid] = cur.r0;
     s_r1[tid] = cur.r1;
-    s_r2[tid] = make_float4(cur.r2.x, cur.r2.y, cur.r2.z, __uint_as_float(cur.idx));
-    if (DEPTH == GS_DEPTH_BLEND) s_z[tid] = cur.z;
+    const bool entry = cur.entry();
+    s_r2[tid] = make_float4(entry ? cur.r2.x : 0.f, entry ? cur.r2.y : 0.f, entry ? cur.r2.z : 0.f,
+                            __uint_as_float(cur.idx));
+    if (DEPTH == GS_DEPTH_BLEND) s_z[tid] = entry ? cur.z : 0.f;
     if (ACC) {
       const int zero = fresh(0);
       s_acc_w[tid] = __hiloint2double(zero, zero);
@@ -813,7 +823,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
 #pragma unroll
         for (int u = 0; u < kFwdUnroll; ++u) {
           // Branch-free per lane: selects keep the state of lanes that skip the
-          // entry or have stopped (staged records are finite, so adding a zero
+          // entry or have stopped (staged colours are finite, so adding a zero
           // weight leaves the colour unchanged).
           const uint64_t pass = has[u] & ~stopped & __builtin_amdgcn_ballot_w64(ee[u] >= op.log2_alpha_min);
           const float Tn = T * (1.f - al[u]);
@@ -922,8 +932,9 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
 // ---------------------------------------------------------------------------
 // One list entry for the backward: the first 48 bytes of its record, with the
 // opacity negated for an inactive entry (a drawn record's opacity is positive),
-// so the walk needs no separate flag.  A corrupt index (outside this view's
-// records) is replaced by an inactive entry with an empty box.
+// so the walk needs no separate flag.  Where there is no entry or its index is
+// corrupt (outside this view's records): an inactive one of zeros with an empty
+// box, so that past a stream's end, too, every product with a weight of 0 is 0.
 struct StagedB {
   int2 box;
   float4 r0, r1, r2;
@@ -937,10 +948,13 @@ __device__ __forceinline__ StagedB fetch_entry_bwd(const float* __restrict__ rec
   r = valid ? r : (uint32_t)vbase;
   const bool act = valid && (!MASKED || active[(int64_t)r - vbase] != 0);
   e.box = valid ? *reinterpret_cast<const int2*>(bin + 4 * (int64_t)r) : make_int2(0xffff, 0xffff);
-  const float4* R4 = reinterpret_cast<const float4*>(rec + (int64_t)r * kRecFloats);
-  e.r0 = R4[0];
-  e.r1 = R4[1];
-  e.r2 = R4[2];
+  e.r0 = e.r1 = e.r2 = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (valid) {
+    const float4* R4 = reinterpret_cast<const float4*>(rec + (int64_t)r * kRecFloats);
+    e.r0 = R4[0];
+    e.r1 = R4[1];
+    e.r2 = R4[2];
+  }
   e.r2.w = act ? fabsf(e.r2.w) : -fabsf(e.r2.w);
   return e;
 }
