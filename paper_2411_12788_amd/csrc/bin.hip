@@ -742,8 +742,14 @@ static int32_t bin_count(const gs_projected_t* proj, const gs_camera_t* cams, in
     if ((st = offsets_by_tile(proj, vs, V, n, t, offsets, tile_order, s)) != GS_OK) return st;
     if ((st = wait_totals(rb, s, t.stats, kTileStats, h)) != GS_OK) return st;
     if ((st = fill_stats(vs, h, stats)) != GS_OK) return st;
-    stats->max_list = (int32_t)h[4];
-    stats->list_slices = (int32_t)h[5];
+    // The records' own counts (bin.w) size the lists, the walk over their boxes
+    // fills them.  If the two differ (records projected with another culling
+    // alpha than proj names, or changed by hand) the radix sort, which keeps
+    // every record inside its own slots, makes the lists.
+    if (h[6] == h[0]) {
+      stats->max_list = (int32_t)h[4];
+      stats->list_slices = (int32_t)h[5];
+    }
     return GS_OK;
   }
   CountWs c = carve_count(ws, nrec);

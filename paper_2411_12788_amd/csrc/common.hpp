@@ -148,20 +148,26 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
 // rounding.  Conservative, so culling with it never changes a result; it
 // drops the entries whose bounding box meets the rectangle but whose
 // (elongated, tilted) ellipse does not.  Host-callable so that a CPU test can
-// check it against brute-force enumeration of pixel centres.
+// check it against brute-force enumeration of pixel centres.  Which products
+// are fused is written out: the kernels that count a record's tiles and those
+// that list them have to decide alike, and what a compiler fuses depends on the
+// code around its copy.
 __host__ __device__ __forceinline__ bool ellipse_meets(float4 r0, float4 r1, int32_t x0, int32_t x1, int32_t y0, int32_t y1,
                                               float log2_alpha_min) {
+#pragma clang fp contract(off)
   const float lx = ((float)x0 + 0.5f - r0.x) - r0.z, hx = ((float)x1 + 0.5f - r0.x) - r0.z;
   const float ly = ((float)y0 + 0.5f - r0.y) - r0.w, hy = ((float)y1 + 0.5f - r0.y) - r0.w;
   if (lx <= 0.f && hx >= 0.f && ly <= 0.f && hy >= 0.f) return true;
   const float A = r1.x, B = r1.y, C = r1.z;
   const float iA = 0.5f / A, iC = 0.5f / C;
-  auto q = [&](float dx, float dy) { return A * dx * dx + B * dx * dy + C * dy * dy; };
+  auto q = [&](float dx, float dy) {
+    return __builtin_fmaf(C * dy, dy, __builtin_fmaf(A * dx, dx, B * dx * dy));
+  };
   const float ya = fminf(fmaxf(-B * lx * iC, ly), hy), yb = fminf(fmaxf(-B * hx * iC, ly), hy);
   const float xa = fminf(fmaxf(-B * ly * iA, lx), hx), xb = fminf(fmaxf(-B * hy * iA, lx), hx);
   const float m = fminf(fminf(q(lx, ya), q(hx, yb)), fminf(q(xa, ly), q(xb, hy)));
   const float budget = r1.w - log2_alpha_min;
-  return m <= budget + 1e-3f * (1.f + fabsf(budget));
+  return m <= __builtin_fmaf(1e-3f, 1.f + fabsf(budget), budget);
 }
 
 

@@ -388,7 +388,9 @@ __global__ __launch_bounds__(kScanT) void k_tile_scan(uint2* __restrict__ ranges
     __shared__ uint32_t s_hist[2][kGroups][kLengthBuckets];
     __shared__ uint32_t s_top[kScanW];
     for (int k = threadIdx.x; k < 2 * kGroups * kLengthBuckets; k += kScanT) (&s_hist[0][0][0])[k] = 0u;
+    __shared__ uint64_t s_all[kScanW];
     uint32_t pairs = 0, slices = 0, longest = 0;
+    uint64_t mine = 0;  // in 64 bits, as the boxes' total
     for (int32_t c0 = 0; c0 < tiles; c0 += kScanT * kScanPer, side ^= 1) {
       const int32_t t0 = c0 + (int32_t)threadIdx.x;
       uint32_t c[kScanPer], at[kScanPer], sl[kScanPer];
@@ -402,6 +404,7 @@ __global__ __launch_bounds__(kScanT) void k_tile_scan(uint2* __restrict__ ranges
         const int32_t t = t0 + j * kScanT;
         c[j] = t < tiles ? c[j] : 0u;
         longest = c[j] > longest ? c[j] : longest;
+        mine += c[j];
         at[j] = c[j];
         sl[j] = slices_of(c[j]);
         some |= sl[j];
@@ -438,12 +441,18 @@ __global__ __launch_bounds__(kScanT) void k_tile_scan(uint2* __restrict__ ranges
       }
     }
     longest = wave_top_u32(longest);
-    if (lane == 0) s_top[w] = longest;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, kWave);
+    if (lane == 0) { s_top[w] = longest; s_all[w] = mine; }
     __syncthreads();
     if (threadIdx.x == 0) {
-      for (int k = 1; k < kScanW; ++k) longest = s_top[k] > longest ? s_top[k] : longest;
+      for (int k = 1; k < kScanW; ++k) {
+        longest = s_top[k] > longest ? s_top[k] : longest;
+        mine += s_all[k];
+      }
       ws.stats[4] = host[4] = longest;
       ws.stats[5] = host[5] = slices;
+      ws.stats[6] = host[6] = mine;
     }
     return;
   }
@@ -848,16 +857,24 @@ __device__ __forceinline__ ListOut list_out(int32_t tile, const ViewSet& vs, int
 }
 
 // Lists of least + 1 .. T ITEMS entries, one workgroup per tile (the others
-// exit).
+// exit).  No list reaches past `pairs`, the entries there is room for, whatever
+// happened to the records between the counting and the placing.
+__device__ __forceinline__ uint2 clamped(uint2 range, uint32_t pairs) {
+  range.y = range.y < pairs ? range.y : pairs;
+  range.x = range.x < range.y ? range.x : range.y;
+  return range;
+}
 template <int T, int ITEMS>
-__global__ __launch_bounds__(T) void k_tile_sort(const uint64_t* __restrict__ entries,
-                                                 const uint2* __restrict__ ranges, uint32_t least, uint32_t zmin,
-                                                 int32_t ibits, int64_t n, uint32_t* __restrict__ vals,
-                                                 uint64_t* __restrict__ keys, ViewSet vs) {
+__global__ __launch_bounds__(T) void k_tile_sort(const uint64_t* __restrict__ entries, uint2* ranges, uint32_t pairs,
+                                                 uint32_t least, uint32_t zmin, int32_t ibits, int64_t n,
+                                                 uint32_t* __restrict__ vals, uint64_t* __restrict__ keys,
+                                                 ViewSet vs) {
   __shared__ SortLds<T, ITEMS> s;
   const int32_t tile = (int32_t)blockIdx.x;
-  const uint2 range = ranges[tile];
+  const uint2 given = ranges[tile], range = clamped(given, pairs);
   const uint32_t len = range.y - range.x;
+  // (the last kernel of the lists is the one that takes all short ones)
+  if (least == 0u && given.y > pairs && threadIdx.x == 0) ranges[tile] = range;
   if (len <= least || len > (uint32_t)(T * ITEMS)) return;
   const ListOut out = list_out(tile, vs, n, zmin, ibits, vals, keys);
   const uint64_t* run = entries + range.x;
@@ -916,7 +933,7 @@ __device__ __forceinline__ uint32_t gather_slice(SortLds<T, ITEMS>& s, const uin
 // takes its slice's two bounds from there, and gathers the slice from the
 // whole run, which is read once per slice, from L2.
 __global__ __launch_bounds__(kLongThreads) void k_tile_sort_long(const uint64_t* __restrict__ entries,
-                                                                 const uint2* __restrict__ ranges,
+                                                                 const uint2* __restrict__ ranges, uint32_t pairs,
                                                                  const uint2* __restrict__ slices, uint32_t zmin,
                                                                  int32_t ibits, int64_t n,
                                                                  uint32_t* __restrict__ vals,
@@ -926,11 +943,12 @@ __global__ __launch_bounds__(kLongThreads) void k_tile_sort_long(const uint64_t*
   const uint2 item = slices[blockIdx.x];
   const int32_t tile = (int32_t)item.x;
   const uint32_t slice = item.y;
-  const uint2 range = ranges[tile];
+  const uint2 range = clamped(ranges[tile], pairs);
   const uint32_t len = range.y - range.x;
   const ListOut out = list_out(tile, vs, n, zmin, ibits, vals, keys);
   const uint64_t* run = entries + range.x;
   const uint32_t count_slices = slices_of(len);
+  if (slice >= count_slices) return;
   uint64_t lo = 0ull, end = ~0ull;
   if (count_slices > 1) {
     // bounds of this slice: quantiles of kSample evenly spaced entries of the run
@@ -1066,7 +1084,8 @@ int32_t offsets_by_tile(const gs_projected_t* proj, const ViewSet& vs, int32_t V
   return GS_OK;
 }
 
-// Whether the lists are sorted by tile.  Every slice of a long list reads the
+// Whether the lists are sorted by tile (max_list is 0 where the pairs were not
+// counted by tile, or came out other than the records say).  Every slice of a long list reads the
 // whole list, so the cost of one list grows with its square.
 bool lists_by_tile_pay(const gs_bin_stats_t* stats) {
   return stats->max_list > 0 && stats->max_list <= kTileMaxList && stats->list_slices <= kMaxSlices;
@@ -1089,15 +1108,16 @@ int32_t lists_by_tile(const gs_projected_t* proj, const ViewSet& vs, int32_t V, 
   else
     hipLaunchKernelGGL(k_tile_place<false>, g.dim, dim3(kBlock), g.lds, s, g.a, r2, zmin, ibits, stats->n_isect,
                        entries, flag, vs);
+  const uint32_t pairs = (uint32_t)stats->n_isect;
   // the longest lists first: they take longest
   if (stats->list_slices > 0)
     hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)stats->list_slices), dim3(kLongThreads), 0, s, entries, r2,
-                       ws.slices, zmin, ibits, n, vals, keys, vs);
+                       pairs, ws.slices, zmin, ibits, n, vals, keys, vs);
   if (stats->max_list > kShortCap)
     hipLaunchKernelGGL((k_tile_sort<kMidThreads, kMidItems>), dim3((unsigned)tiles), dim3(kMidThreads), 0, s, entries,
-                       r2, (uint32_t)kShortCap, zmin, ibits, n, vals, keys, vs);
+                       r2, pairs, (uint32_t)kShortCap, zmin, ibits, n, vals, keys, vs);
   hipLaunchKernelGGL((k_tile_sort<kShortThreads, kShortItems>), dim3((unsigned)tiles), dim3(kShortThreads), 0, s,
-                     entries, r2, 0u, zmin, ibits, n, vals, keys, vs);
+                     entries, r2, pairs, 0u, zmin, ibits, n, vals, keys, vs);
   MS_CHECK_LAUNCH("tile lists");
   return GS_OK;
 }

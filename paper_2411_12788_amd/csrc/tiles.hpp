@@ -18,7 +18,7 @@ constexpr int32_t kSliceKeys = 4096;       // aimed entries of a longer list's s
 constexpr int32_t kSample = 1024;          // entries that bound the slices
 constexpr int32_t kMaxSlices = 1 << 16;    // slices over all lists
 constexpr int32_t kTileMaxList = 65536;    // longer lists: the radix sort
-constexpr int kTileStats = 6;              // n_isect, n_visible, zmin, zmax, longest list, slices
+constexpr int kTileStats = 7;              // n_isect, n_visible, zmin, zmax, longest list, slices, pairs by tile
 
 // Workgroups that sort a list of more than kMidCap entries (0: a shorter one).
 __host__ __device__ inline uint32_t slices_of(uint32_t len) {
