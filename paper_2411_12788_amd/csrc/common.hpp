@@ -120,6 +120,16 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
   return (uint64_t)uniform_u32((uint32_t)x) | ((uint64_t)uniform_u32((uint32_t)(x >> 32)) << 32);
 }
 
+// Orders a wave's LDS accesses: its lanes read what others of its lanes wrote, or
+// write what others have read.  (No instruction: a wave's LDS accesses are in
+// order, the compiler is told to keep them so in both directions.)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// 32-bit accesses to LDS arrays of smaller elements.
+typedef uint32_t __attribute__((may_alias)) AliasedU32;
+
 // Wave-wide reductions over 64 lanes.
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll

@@ -416,9 +416,7 @@ __device__ __forceinline__ void make_streams(const RoundLds<BATCH, PER_CHUNK>& s
       for (int c = 0; c < kChunks; ++c) n[g] += put(g, c, n[g]);
     }
   }
-  // the lanes of this wave read what other lanes of it have written
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
 }
 template <typename T>
 __device__ __forceinline__ T lds_at(const T* base, uint32_t bytes) {
@@ -446,9 +444,9 @@ __device__ __forceinline__ void retest_chunk(uint16_t* stream, int from, int unt
   const uint64_t m = __builtin_amdgcn_ballot_w64(rel);
   // each lane of a slot writes one: the entries in order, then the empty ones
   const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  wave_sync();
   if (slot) stream[from + (rel ? below : (int)__popcll(m) + lane - below)] = (uint16_t)(rel ? off : kNoEntry);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
 }
 __device__ __forceinline__ int max4(const int (&n)[kGroups]) {
   const int a = n[0] > n[1] ? n[0] : n[1], b = n[2] > n[3] ? n[2] : n[3];
@@ -608,7 +606,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   __shared__ uint16_t s_stream[kWaves][kGroups][kFwdBatch];
   // an offset read past a stream's end is unused, but it is read: keep it in range
   for (int q = threadIdx.x; q < kWaves * kGroups * kFwdBatch / 2; q += kBlock)
-    reinterpret_cast<uint32_t*>(&s_stream[0][0][0])[q] = 0;
+    reinterpret_cast<AliasedU32*>(&s_stream[0][0][0])[q] = 0;
   const WorkItem wi = work_item(order, ranges, nsplit, vs.tiles_total, true);
   if (wi.skip) return;
   const int32_t tile = wi.tile;
@@ -795,7 +793,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
       int mine = group == 0 ? n4[0] : group == 1 ? n4[1] : group == 2 ? n4[2] : n4[3];
       const int longest = (int)uniform_u32((uint32_t)(rp ? 0 : max4(n4)));
       const uint16_t* stream = &s_stream[wv][group][0];
-      uint32_t pair = *reinterpret_cast<const uint32_t*>(stream);
+      uint32_t pair = *reinterpret_cast<const AliasedU32*>(stream);
       for (int i = 0; i < longest; i += kFwdUnroll) {
         uint32_t off[kFwdUnroll];
         uint64_t has[kFwdUnroll];
@@ -805,7 +803,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
           off[u] = (pair >> (16 * u)) & 0xffffu;
         }
         const int next = i + kFwdUnroll < kFwdBatch ? i + kFwdUnroll : i;
-        pair = *reinterpret_cast<const uint32_t*>(stream + next);
+        pair = *reinterpret_cast<const AliasedU32*>(stream + next);
         float4 q2[kFwdUnroll];
         float al[kFwdUnroll], ee[kFwdUnroll], wg[kFwdUnroll];
 #pragma unroll
@@ -1136,7 +1134,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   __shared__ uint8_t s_stream[kWaves][kGroups][kBatch];
   __shared__ uint32_t s_last[kWaves * kGroups];  // largest `last` of each group
   for (int q = threadIdx.x; q < kWaves * kGroups * kBatch / 4; q += kBlock)
-    reinterpret_cast<uint32_t*>(&s_stream[0][0][0])[q] = 0;
+    reinterpret_cast<AliasedU32*>(&s_stream[0][0][0])[q] = 0;
   if (!DET)
     for (int q = threadIdx.x; q < kBatch * kG2d; q += kBlock) s_acc[q] = Acc(0);
   const WorkItem wi = work_item(order, ranges, nsplit, vs.tiles_total, false);
@@ -1351,8 +1349,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       if (__builtin_amdgcn_inverse_ballot_w64(walked))
         list[__builtin_amdgcn_mbcnt_hi((uint32_t)(walked >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)walked, 0u))] =
             (uint8_t)(wv * kWave + fl);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
 #pragma unroll 1
       for (int e = fe < kWave / kG2d ? fe : kWave; e < cnt; e += kWave / kG2d) {
         const uint32_t k = list[e];

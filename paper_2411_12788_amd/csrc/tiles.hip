@@ -45,11 +45,6 @@ struct WalkLds {  // of one wave
   uint32_t mark[kWave];       // 0 between turns
   float4 r0[CULL ? kWave : 1], r1[CULL ? kWave : 1];
 };
-// Orders a wave's LDS accesses: its lanes read what others of its lanes wrote.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
@@ -135,6 +130,7 @@ __device__ __forceinline__ void for_each_tile(WalkLds<CULL>& L, int4 b, int64_t 
     const uint64_t m = __builtin_amdgcn_ballot_w64(L.mark[lane] != 0u);
     wave_sync();
     if (nxt < (uint32_t)kWave) L.mark[nxt] = 0u;
+    wave_sync();
     const uint32_t t = c0 + (uint32_t)lane;
     const uint32_t own = own0 + lanes_below(m) + (uint32_t)((m >> lane) & 1ull);
     if (t < total) visit(own, t - L.start[own]);
