@@ -192,6 +192,15 @@ __host__ __device__ __forceinline__ bool tile_kept(float4 r0, float4 r1, int32_t
   return ellipse_meets(r0, r1, px0, px1, py0, py1, log2_alpha);
 }
 
+// Backward: byte offset in a round of 16-byte staged entries from which on a
+// pixel composited nothing; its last entry is list position `last` - 1, the
+// round holds positions [first, first + batch), `batch` of them at most (a list
+// may hold 2^28 entries and more, 16 times which is no 32-bit number).
+__host__ __device__ __forceinline__ uint32_t round_limit(uint32_t last, uint32_t first, uint32_t batch) {
+  const uint32_t ahead = last > first ? last - first : 0u;
+  return (ahead < batch ? ahead : batch) * 16u;
+}
+
 }  // namespace msplat
 
 #define MS_CHECK_LAUNCH(where)                                         \

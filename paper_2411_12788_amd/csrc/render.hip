@@ -1240,7 +1240,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       int n4[kGroups];
       make_streams<false>(s_round, s_stream[wv], 1, rp, rp, wv, fresh(lane), n4);
       // round-relative offset from which on the pixel composited nothing
-      const uint32_t lim = lst > base - start ? (lst - (base - start)) * 16u : 0u;
+      const uint32_t lim = round_limit(lst, base - start, kBatch);
       // Split work item: row r takes the r-th latest of the next four entries
       // of the group's stream.  The transmittance in front of each is the
       // product of 1 / (1 - alpha) over the rows up to it, its suffix colour
