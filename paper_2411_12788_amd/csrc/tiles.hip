@@ -262,7 +262,9 @@ __global__ __launch_bounds__(kBlock) void k_tile_start(TileArgs a, uint32_t* __r
 __device__ __forceinline__ bool in_order(const uint2* __restrict__ sample) {
   static_assert(kSampleGroups == kWave, "one sample per lane");
   const uint2 x = sample[lane_id()];
-  return 2 * (uint64_t)last_lane(wave_scan_u32(x.x)) <= kTilesPerTwoPairs * (uint64_t)last_lane(wave_scan_u32(x.y));
+  // (64 rectangles of at most 2^24 tiles fit 32 bits, 64 times 2^27 pairs do not)
+  const uint64_t pairs = ((uint64_t)last_lane(wave_scan_u32(x.y >> 16)) << 16) + last_lane(wave_scan_u32(x.y & 0xffffu));
+  return 2 * (uint64_t)last_lane(wave_scan_u32(x.x)) <= kTilesPerTwoPairs * pairs;
 }
 
 // ---------------------------------------------------------------------------

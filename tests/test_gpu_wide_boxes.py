@@ -77,3 +77,26 @@ def test_cost_does_not_grow_with_the_bands(gpu_lib):
     a, b = ms(lists), ms(sorted_lists)
     print(f"by tile {a:.2f} ms, radix {b:.2f} ms", flush=True)
     assert a < 0.5 * b
+
+
+def test_sampled_pairs_beyond_32_bits(gpu_lib):
+    """256 records over the whole of an 8192x8192 view: the one group of records,
+    sampled 64 times by the choice of path, has 2^26 pairs, 2^32 in all, which
+    is not none."""
+    import ctypes
+    from paper_2411_12788_amd import _lib as L
+    from tests.test_gpu_tile_lists import _Cam, _projected
+    R, side = H.raster(), 8192
+    cam = _Cam(side, side)
+    proj = _projected(R, [cam], [(0, side - 1, 0, side - 1)] * 256, np.linspace(1.0, 2.0, 256))
+    n, tiles, lib = 256, R.tiles_total([cam]), L.lib()
+    offsets = torch.empty(n, dtype=torch.int32, device="cuda")
+    ranges = torch.empty(2 * tiles, dtype=torch.int32, device="cuda")
+    order = torch.empty(tiles, dtype=torch.int32, device="cuda")
+    ws = torch.empty(lib.gs_bin_count_workspace_size(n), dtype=torch.uint8, device="cuda")
+    st, pc = L.BinStats(), proj.c()
+    L.check(lib.gs_bin_tiles(ctypes.byref(pc), R.cameras([cam]), 1, n, R._ptr(offsets), ctypes.byref(st),
+                             R._ptr(ranges), R._ptr(order), R._ptr(ws), ws.numel(), R._stream()), "gs_bin_tiles")
+    torch.cuda.synchronize()
+    assert st.n_isect == 256 * tiles == 1 << 26
+    assert st.max_list == 256
