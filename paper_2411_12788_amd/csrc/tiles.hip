@@ -239,12 +239,21 @@ __device__ __forceinline__ void walk_rows(WalkLds<CULL>& L, const TileArgs& a, i
 // 1,041 against 623 and 678 us (11 per pair); 500k records, 1.2M pairs 99 and
 // 223 against 193 and 200 us (6.5); 200k records 87 and 127 against 156 and
 // 153 us (5).
+// The other end is a group whose boxes are nearly all as large as the largest:
+// a group's pairs are one workgroup's work here (1.3 ns a pair for the three
+// walks) and a record's boxes one thread's in the radix sort's emission (0.16 us
+// a tile of the largest box), so the radix sort is faster above 128 times the
+// largest box.  512 records over all of a 1920x1080 view 2.74 ms by tile and
+// 1.55 by radix sort, 64 of them 0.77 and 1.45, 256 of them beside 4,096 small
+// ones 0.53 and 1.62.  Below kMostGroupPairs both take much the same (256 over
+// a 256x256 view: 156 and 157 us).
 constexpr uint64_t kTilesPerTwoPairs = 11;
+constexpr uint32_t kMostGroupPairs = 1u << 16, kMostBoxes = 128;
 
 __global__ __launch_bounds__(kBlock) void k_tile_start(TileArgs a, uint32_t* __restrict__ ranges, int64_t words,
-                                                       int64_t groups, uint2* __restrict__ sample) {
+                                                       int64_t groups, uint4* __restrict__ sample) {
   __shared__ RectLds s_rect;
-  __shared__ uint32_t s_sum[kWaves];
+  __shared__ uint32_t s_sum[kWaves], s_box[kWaves];
   for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < words; k += (int64_t)gridDim.x * kBlock)
     ranges[k] = 0u;
   if (blockIdx.x >= (unsigned)kSampleGroups) return;
@@ -253,15 +262,22 @@ __global__ __launch_bounds__(kBlock) void k_tile_start(TileArgs a, uint32_t* __r
   const int4 b = i < a.n ? a.bin[i] : make_int4(0, 0, 0, 0);
   const TileRect r = block_rect(s_rect, b, 1 << 12, 1 << 12);
   const uint32_t sum = wave_scan_u32(b.w > 0 ? (uint32_t)b.w : 0u);
-  if ((threadIdx.x & (kWave - 1)) == kWave - 1) s_sum[threadIdx.x / kWave] = sum;
+  const uint32_t box = wave_top_u32(b.w > 0 ? (uint32_t)b.w : 0u);
+  if ((threadIdx.x & (kWave - 1)) == kWave - 1) {
+    s_sum[threadIdx.x / kWave] = sum;
+    s_box[threadIdx.x / kWave] = box;
+  }
   __syncthreads();
   if (threadIdx.x == 0)
-    sample[blockIdx.x] = make_uint2((uint32_t)(r.w * r.h), s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]);
+    sample[blockIdx.x] = make_uint4((uint32_t)(r.w * r.h), s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3],
+                                    max(max(s_box[0], s_box[1]), max(s_box[2], s_box[3])), 0u);
 }
 // Whether the pairs are worth counting by tile (the same in every workgroup).
-__device__ __forceinline__ bool in_order(const uint2* __restrict__ sample) {
+__device__ __forceinline__ bool worth_it(const uint4* __restrict__ sample) {
   static_assert(kSampleGroups == kWave, "one sample per lane");
-  const uint2 x = sample[lane_id()];
+  const uint4 x = sample[lane_id()];
+  const uint32_t most = wave_top_u32(x.y);
+  if (most > kMostGroupPairs && most > (uint64_t)kMostBoxes * wave_top_u32(x.z)) return false;
   // (64 rectangles of at most 2^24 tiles fit 32 bits, 64 times 2^27 pairs do not)
   const uint64_t pairs = ((uint64_t)last_lane(wave_scan_u32(x.y >> 16)) << 16) + last_lane(wave_scan_u32(x.y & 0xffffu));
   return 2 * (uint64_t)last_lane(wave_scan_u32(x.x)) <= kTilesPerTwoPairs * pairs;
@@ -286,7 +302,7 @@ __global__ __launch_bounds__(kBlock) void k_tile_count(TileArgs a, uint2* __rest
   const int32_t tiles_x = vs.v[v].tiles_x;
   const TileRect r = block_rect(s_rect, b, tiles_x, vs.v[v].tiles_y);
   const int32_t fit = r.w > 0 ? a.table / r.w : 1;
-  const int32_t height = in_order(ws.sample) ? r.h : 0;
+  const int32_t height = worth_it(ws.sample) ? r.h : 0;
   for (int32_t y = 0; y < height; y += fit) {
     const int32_t rows = r.h - y < fit ? r.h - y : fit, cells = rows * r.w;
     __syncthreads();  // the previous band's table is read
@@ -1034,7 +1050,7 @@ size_t tile_ws_bytes(int64_t nrec) {
   const int64_t nb = max_blocks(nrec);
   return 4 * align256(nb * 4) + align256(kTileStats * 8) +
          align256((size_t)kMaxOrderGroups * kLengthBuckets * 4) + align256((size_t)kMaxSlices * 8) +
-         align256((size_t)kMaxOrderGroups * kOrderTiles) + align256((size_t)kSampleGroups * 8);
+         align256((size_t)kMaxOrderGroups * kOrderTiles) + align256((size_t)kSampleGroups * 16);
 }
 
 TileWs carve_tiles(void* ws, int64_t nrec) {
@@ -1049,7 +1065,7 @@ TileWs carve_tiles(void* ws, int64_t nrec) {
   t.hist = reinterpret_cast<uint32_t*>(p); p += align256((size_t)kMaxOrderGroups * kLengthBuckets * 4);
   t.slices = reinterpret_cast<uint2*>(p); p += align256((size_t)kMaxSlices * 8);
   t.bucket = reinterpret_cast<uint8_t*>(p); p += align256((size_t)kMaxOrderGroups * kOrderTiles);
-  t.sample = reinterpret_cast<uint2*>(p);
+  t.sample = reinterpret_cast<uint4*>(p);
   return t;
 }
 

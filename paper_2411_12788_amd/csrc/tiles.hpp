@@ -34,7 +34,7 @@ struct TileWs {
   uint64_t* stats;   // [kTileStats]
   uint32_t* hist;    // [groups][kLengthBuckets]
   uint8_t* bucket;   // [tiles] length bucket
-  uint2* sample;     // [kSampleGroups] (tiles of the rectangle, pairs)
+  uint4* sample;     // [kSampleGroups] (tiles of the rectangle, pairs, tiles of the largest box, -)
   uint2* slices;     // [kMaxSlices] (tile, slice) of the lists of more than kMidCap entries
 };
 

@@ -79,17 +79,13 @@ def test_cost_does_not_grow_with_the_bands(gpu_lib):
     assert a < 0.5 * b
 
 
-def test_sampled_pairs_beyond_32_bits(gpu_lib):
-    """256 records over the whole of an 8192x8192 view: the one group of records,
-    sampled 64 times by the choice of path, has 2^26 pairs, 2^32 in all, which
-    is not none."""
+def _tiles(R, cam, boxes):
+    """gs_bin_tiles alone of one view's boxes: the statistics."""
     import ctypes
     from paper_2411_12788_amd import _lib as L
-    from tests.test_gpu_tile_lists import _Cam, _projected
-    R, side = H.raster(), 8192
-    cam = _Cam(side, side)
-    proj = _projected(R, [cam], [(0, side - 1, 0, side - 1)] * 256, np.linspace(1.0, 2.0, 256))
-    n, tiles, lib = 256, R.tiles_total([cam]), L.lib()
+    from tests.test_gpu_tile_lists import _projected
+    n, tiles, lib = len(boxes), R.tiles_total([cam]), L.lib()
+    proj = _projected(R, [cam], boxes, np.linspace(1.0, 2.0, n))
     offsets = torch.empty(n, dtype=torch.int32, device="cuda")
     ranges = torch.empty(2 * tiles, dtype=torch.int32, device="cuda")
     order = torch.empty(tiles, dtype=torch.int32, device="cuda")
@@ -98,5 +94,19 @@ def test_sampled_pairs_beyond_32_bits(gpu_lib):
     L.check(lib.gs_bin_tiles(ctypes.byref(pc), R.cameras([cam]), 1, n, R._ptr(offsets), ctypes.byref(st),
                              R._ptr(ranges), R._ptr(order), R._ptr(ws), ws.numel(), R._stream()), "gs_bin_tiles")
     torch.cuda.synchronize()
-    assert st.n_isect == 256 * tiles == 1 << 26
-    assert st.max_list == 256
+    return st
+
+
+@pytest.mark.parametrize("side,n,by_tile", [
+    (1024, 128, True),    # half of a workgroup's records as large as the largest
+    (1024, 129, False),   # more: one workgroup would do all the work
+    (1024, 513, False),
+    (256, 256, True),     # few pairs: no matter
+    (8192, 256, False),   # 2^26 pairs in the one group, sampled 64 times: 2^32 in all
+])
+def test_groups_of_boxes_as_large_as_the_view(gpu_lib, side, n, by_tile):
+    from tests.test_gpu_tile_lists import _Cam
+    R = H.raster()
+    st = _tiles(R, _Cam(side, side), [(0, side - 1, 0, side - 1)] * n)
+    assert st.n_isect == n * (side // 16) ** 2
+    assert st.max_list == (n if by_tile else 0)
