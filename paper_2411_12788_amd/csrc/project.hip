@@ -144,12 +144,16 @@ __device__ __forceinline__ void camera_centre(const KView& cam, double* c) {
     c[k] = -((double)cam.R[k] * cam.t[0] + (double)cam.R[3 + k] * cam.t[1] + (double)cam.R[6 + k] * cam.t[2]);
 }
 
-// Several views of at least this many Gaussians: one thread per Gaussian
-// (k_project_views) instead of one per record.  Below, one thread per record
-// has the waves to hide its latency: 32,768 Gaussians in 8 views 18 us against
-// 22, in 16 views 27 against 36; 65,536 in 8 views 28 against 24, in 16 views 46
-// against 39; with 2 to 4 views both are alike there and 3 to 24 % apart at
-// 500,000 and more.
+// Several views of at least this many Gaussians without tile culling: one thread
+// per Gaussian (k_project_views) instead of one per record.  Below, one thread
+// per record has the waves to hide its latency (32,768 Gaussians: both alike).
+// Above, surfaces at 1280x720: 200k in 2 / 4 / 16 views 24 / 38 / 126 us by
+// record and 24 / 32 / 94 by Gaussian; 500k 45 / 83 / 300 and 39 / 64 / 222; 1.5M
+// in 2 / 4 / 8 views 156 / 297 / 582 and 123 / 192 / 339.  With tile culling the
+// lanes of a wave count different numbers of tiles, view after view: a cube of
+// 200k in 4 / 16 views 102 / 331 us by record and 153 / 570 by Gaussian, 1.5M in
+// 4 views 612 and 826; surfaces 47 / 136 and 55 / 200 (wide ones of 1.5M gain,
+// 323 -> 229 us, but nothing known before the projection tells them apart).
 constexpr int64_t kViewsMinRows = 1 << 16;
 struct ProjArgs {
   SceneArgs sc;
@@ -162,8 +166,9 @@ struct ProjArgs {
 
 // One record: geometry g in view `cam`, opacity o, to row r.  log_ratio():
 // 2 ln(o / alpha_min); p(k): the centre; fetch_sh() runs before the first sh(k),
-// plane k of the SH coefficients, and only for a record drawn.
-template <int DEG, typename Kk, typename Centre, typename Fetch, typename Sh>
+// plane k of the SH coefficients, and only for a record drawn.  CULL: tile
+// culling may be asked for.
+template <int DEG, bool CULL, typename Kk, typename Centre, typename Fetch, typename Sh>
 __device__ __forceinline__ void project_record(const ProjArgs& pa, const KView& cam, int64_t r, const Geo& g, double o,
                                                const Kk& log_ratio, const Centre& p, bool culled,
                                                const Fetch& fetch_sh, const Sh& sh) {
@@ -221,7 +226,7 @@ __device__ __forceinline__ void project_record(const ProjArgs& pa, const KView& 
     const float4 r0 = make_float4(uh, vh, (float)(g.u - (double)uh), (float)(g.v - (double)vh));
     const float4 r1 = make_float4((float)(0.5 * log2e * g.a), (float)(log2e * g.b), (float)(0.5 * log2e * g.c),
                                   (float)log2(o));
-    if (pa.tile_cull < 0.f && tiles <= GS_TILE_CULL_MAX_TILES && tiles > 1) {
+    if (CULL && pa.tile_cull < 0.f && tiles <= GS_TILE_CULL_MAX_TILES && tiles > 1) {
       // count only the tiles the record's alpha can reach (emission repeats the test)
       int32_t kept = 0;
       for (int32_t ty = ylo >> 4; ty <= (yhi >> 4); ++ty)
@@ -245,18 +250,15 @@ __device__ __forceinline__ void project_record(const ProjArgs& pa, const KView& 
   reinterpret_cast<int4*>(pa.bin)[r] = b4;
 }
 
-// One thread per record.  Bound by memory: a Gaussian's 236 bytes once, 80
-// bytes per record.  The views of one block of Gaussians are projected by
-// consecutive workgroups of one XCD (workgroups go to the eight XCDs in turn),
-// so only the first of them reads the block from HBM and the others find it
-// in that XCD's L2; with the views one after the other the scene was read
-// once per view (1M Gaussians in 16 views, which k_project_views takes now:
-// 1467 us against 1180).
+// One thread per record.  Bound by memory: a Gaussian's 236 bytes, 80 bytes per
+// record, and with tile culling by the tests of its tiles.  (The views of a block
+// of Gaussians one after the other on one XCD read the scene from HBM once, but
+// take 102 registers for 80, lose 3 to 10 % with tile culling and are slower than
+// k_project_views without.)
 template <int DEG>
 __global__ __launch_bounds__(kBlock) void k_project(ProjArgs pa, ViewSet vs) {
-  const uint32_t turn = blockIdx.x >> 3, group = turn / (uint32_t)vs.count;
-  const int v = (int)(turn - group * (uint32_t)vs.count);
-  const int64_t i = ((int64_t)group * 8 + (blockIdx.x & 7)) * kBlock + threadIdx.x;
+  const int v = (int)blockIdx.y;
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int64_t n = pa.sc.n;
   if (i >= n) return;
   const KView& cam = vs.v[v];
@@ -265,7 +267,7 @@ __global__ __launch_bounds__(kBlock) void k_project(ProjArgs pa, ViewSet vs) {
   geometry(cam, pa.op, pa.sc, i, g);
   const double o = pa.sc.opacity[i];
   const float* shp = pa.sc.sh;
-  project_record<DEG>(
+  project_record<DEG, true>(
       pa, cam, r, g, o, [&] { return 2.0 * log(o / (double)pa.op.alpha_min); },
       [&](int k) { return (double)pa.sc.means[k * n + i]; }, pa.cull && pa.cull[i] == 0, [] {},
       [&](int k) { return shp[(int64_t)k * n + i]; });
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     geometry_centre(vs.v[v], pa.op, p, g);
     g.ok = g.ok && turned;
     geometry_view(vs.v[v], pa.op, g);
-    project_record<DEG>(
+    project_record<DEG, false>(
         pa, vs.v[v], (int64_t)v * n + i, g, o, [&] { return kk; }, [&](int k) { return p[k]; }, culled,
         [&] {
           if (have) return;
@@ -598,7 +600,7 @@ extern "C" int32_t gs_project(const gs_scene_t* scene, const gs_camera_t* cams, 
   pa.op = make_kopts(opts);
   pa.tile_cull = out->tile_cull_log2_alpha < 0.f ? out->tile_cull_log2_alpha : 0.f;
   hipStream_t s = (hipStream_t)stream;
-  if (V >= 2 && scene->n >= kViewsMinRows) {
+  if (V >= 2 && scene->n >= kViewsMinRows && !(pa.tile_cull < 0.f)) {
     const dim3 grid((unsigned)grid_1d(scene->n));
     switch (scene->sh_degree) {
       case 0: hipLaunchKernelGGL(k_project_views<0>, grid, dim3(kBlock), 0, s, pa, vs); break;
@@ -609,8 +611,7 @@ extern "C" int32_t gs_project(const gs_scene_t* scene, const gs_camera_t* cams, 
     MS_CHECK_LAUNCH("project");
     return GS_OK;
   }
-  const int64_t blocks = (grid_1d(scene->n) + 7) / 8 * 8 * V;  // n V < 2^32: fits
-  const dim3 grid((unsigned)blocks);
+  const dim3 grid((unsigned)grid_1d(scene->n), (unsigned)V);
   switch (scene->sh_degree) {
     case 0: hipLaunchKernelGGL(k_project<0>, grid, dim3(kBlock), 0, s, pa, vs); break;
     case 1: hipLaunchKernelGGL(k_project<1>, grid, dim3(kBlock), 0, s, pa, vs); break;
