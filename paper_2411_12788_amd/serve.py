@@ -246,10 +246,13 @@ class GpuExecutor:
         self.pairs_per_record: Dict[Any, float] = {}
         self.lock = threading.Lock()
 
-    # bytes held by one batch (records, lists, sort workspace, outputs)
+    # bytes held by one batch: records and offsets, lists, the binning's two
+    # workspaces (whose sizes the library states), outputs; ranges and tile
+    # order (12 bytes a tile) and the rounding of small blocks in the constant
     def _bytes(self, n: int, V: int, P: int, n_isect: int) -> int:
-        rec = V * n * (64 + 16 + 4) + 8 * ((V * n) // 4096 + 1) * 8
-        pairs = n_isect * (4 + 8 + 4 + 8 + 4) + (n_isect // 4096 + 1) * 256 * 4 * 2
+        lib = self.R.L.lib()
+        rec = V * n * (64 + 16 + 4) + lib.gs_bin_count_workspace_size(V * n)
+        pairs = n_isect * 4 + lib.gs_bin_sort_workspace_size(n_isect)
         frame = P * (12 + 4 + 4 + 4 + 4)
         return int(rec + pairs + frame) + (1 << 20)
 
