@@ -137,13 +137,14 @@ __global__ __launch_bounds__(kBlock) void k_morton_code(const float* __restrict_
   if (codes) codes[i] = code;
 }
 
-// Eight rows per thread: the order's rows are anywhere in a plane, and with one
+// Four rows per thread: the order's rows are anywhere in a plane, and with one
 // gather of a lane in flight the latency of L2 and the memory behind it bounds
-// the copy (1.2M Gaussians of 59 planes: one row 220 us, four 138, eight 129,
-// sixteen 144; a straight copy of as many bytes takes 110).  Planes one after
-// the other: a plane is read by all XCDs at a time and stays in the
-// memory-side cache; one plane per XCD measured the same (136).
-constexpr int kPermuteRows = 8;
+// the copy (48 planes of 1M Gaussians whose appended rows return to their places:
+// one row 170 us, two 144, four 137, eight 136).  More rows leave fewer workgroups
+// a plane, so more planes are read at a time than an XCD's L2 holds, which an
+// order without any locality feels (the first one of a scene in random order: one
+// row 333 us, four 334, eight 380).
+constexpr int kPermuteRows = 4;
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_permute(const T* __restrict__ src, T* __restrict__ dst, int64_t planes,
                                                     int64_t n, const uint32_t* __restrict__ perm) {
