@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kBlock) void k_render_fwd(const float* __restrict__
   // (double, and one lane per group: see row_sum_max2)
   __shared__ double s_acc_w[ACC ? kFwdBatch : 1];
   __shared__ uint32_t s_acc_m[ACC ? kFwdBatch : 1];
-  __shared__ uint16_t s_stream[kWaves][kGroups][kFwdBatch];
+  __shared__ alignas(4) uint16_t s_stream[kWaves][kGroups][kFwdBatch];
   // an offset read past a stream's end is unused, but it is read: keep it in range
   for (int q = threadIdx.x; q < kWaves * kGroups * kFwdBatch / 2; q += kBlock)
     reinterpret_cast<AliasedU32*>(&s_stream[0][0][0])[q] = 0;
@@ -960,29 +960,26 @@ __device__ __forceinline__ StagedB fetch_entry_bwd(const float* __restrict__ rec
 // The nine sums of an entry over each 16-lane row (4x4 pixels): of six per-lane
 // partials p, and of the weight w times the three channels of dL/dcolour.
 //
-// Partials: the four lanes of a quad (lane xor 1, then xor 2), then lanes 8
-// apart (a row rotate), then the two quads of a half row (its mirror: the lanes
-// of a quad hold the same value by then).  The last two steps keep one value in
-// either half (values 2 j and 2 j + 1 share a register), chosen by the bank mask
-// of the add itself (lanes of a disabled bank keep the register's value), so a
-// pair of values costs two instructions and no selects, which the compiler
-// cannot express: hence the assembly.  Starting with the halves takes 13
-// instructions instead of 21 and was not kept: the gradient of a needle's scales
-// is a difference of the second moments smaller than they are by the square of
-// its elongation, so it shows every rounding in which the three differ, and
-// another tree (with the scalar suffix, see alpha_gradient) moved it by three
-// times the noise of the atomics.  Channels: lane m of a quad sums
-// channel m over the quad's pixels, w of each pixel by a broadcast inside the
-// quad times that pixel's channel m (gm, the same for all entries), then the
-// four quads are added: six instructions instead of three products and ten.  A
-// DPP read needs two instructions after the write of its register; the order
-// below keeps that distance.  Returned: in lane L of a row the total of value
-// sum_slot(L), where that is not negative.
+// Partials: lanes 1 apart, 2 apart, 8 apart, 4 apart.  The first two steps keep
+// one of two values in either lane (selects), the third one of two registers in
+// either half of the row, chosen by the bank mask of the add itself (lanes of a
+// disabled bank keep the register's value), which the compiler cannot express:
+// hence the assembly.  The last, a rotate by 4, is right where bit 2 of the lane
+// is set.  Halves first, all by bank masks, takes 13 instructions instead of 16
+// and was not kept: the gradient of a needle's scales is a difference of the
+// second moments smaller than they are by the square of its elongation, so it
+// shows every rounding in which the three differ, and another tree (with the
+// scalar suffix, see alpha_gradient) moved it by three times the noise of the
+// atomics.  Channels: lane m of a quad sums channel m over the quad's pixels, w
+// of each pixel by a broadcast inside the quad times that pixel's channel m (gm,
+// the same for all entries), then the four quads are added: six instructions
+// instead of three products and ten.  A DPP read needs two instructions after
+// the write of its register; the order below keeps that distance.  Returned: in
+// lane L of a row the total of value sum_slot(L), where that is not negative.
 __device__ __forceinline__ int sum_slot(int lane) {
-  const int q = (lane >> 2) & 3, r = lane & 3;
-  if (r == 3) return 2 * (q & 1) + (q >> 1);  // quads hold values 0, 2, 1, 3
-  if (q == 0) return 6 + r;
-  return r == 0 && q < 3 ? 3 + q : -1;  // values 4 and 5 in the halves of the row
+  const int l = lane & 15;
+  if (l & 4) return l < 8 ? l - 4 : l < 14 ? l - 8 : -1;
+  return l < 3 ? 6 + l : -1;
 }
 struct ChannelPixels {
   float x[4];  // lane m of a quad: channel m of the quad's pixels
@@ -1003,39 +1000,32 @@ __device__ __forceinline__ ChannelPixels channel_pixels(float g0, float g1, floa
   return r;
 }
 __device__ __forceinline__ float row_sum9(const float (&p)[6], float w, const ChannelPixels& gm, int lane) {
-  float q0 = p[0], q1 = p[1], q2 = p[2], q3 = p[3], q4 = p[4], q5 = p[5], a, b, c, d, f, h;
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E;
+  const bool odd = (lane & 1) != 0, upper = (lane & 2) != 0;
+  float a[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const float keep = odd ? p[2 * j + 1] : p[2 * j], send = odd ? p[2 * j] : p[2 * j + 1];
+    a[j] = keep + dpp_take<kXor1>(send);
+  }
+  const float b = (upper ? a[1] : a[0]) + dpp_take<kXor2>(upper ? a[0] : a[1]);
+  const float c = a[2] + dpp_take<kXor2>(a[2]);
+  float d, h;
   asm("s_nop 1\n\t"
-      "v_mul_f32_dpp %5, %12, %13 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %6, %6, %6 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %7, %7, %7 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %8, %8, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %9, %9, %9 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %10, %10, %10 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %11, %11, %11 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %5, %12, %14 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %7, %7, %7 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %8, %8, %8 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %9, %9, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %10, %10, %10 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %11, %11, %11 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f32_dpp %5, %12, %15 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %0, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %1, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-      "v_fmac_f32_dpp %5, %12, %16 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %0, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %2, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-      "v_add_f32_dpp %5, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %3, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-      "v_add_f32_dpp %3, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-      "v_add_f32_dpp %4, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-      "v_add_f32_dpp %5, %5, %5 row_ror:4 row_mask:0xf bank_mask:0xf"
-      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d), "=&v"(f), "=&v"(h), "+v"(q0), "+v"(q1), "+v"(q2), "+v"(q3), "+v"(q4),
-        "+v"(q5)
-      : "v"(w), "v"(gm.x[0]), "v"(gm.x[1]), "v"(gm.x[2]), "v"(gm.x[3]));
-  return (lane & 3) == 3 ? d : (lane & 12) == 0 ? h : f;
+      "v_mul_f32_dpp %1, %4, %5 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_fmac_f32_dpp %1, %4, %6 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_fmac_f32_dpp %1, %4, %7 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %8 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %1, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xf"
+      : "=&v"(d), "=&v"(h)
+      : "v"(b), "v"(c), "v"(w), "v"(gm.x[0]), "v"(gm.x[1]), "v"(gm.x[2]), "v"(gm.x[3]));
+  return (lane & 4) != 0 ? d : h;
 }
 
 // dL/dalpha of one entry of a pixel, with the transmittance T in front of it,
@@ -1109,11 +1099,13 @@ __device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ par
 // ~17 G requests/s), which bounded the kernel where most entries are active
 // (1M Gaussians, 16 views, 17.3M pixels, all active: 169M -> 31M requests).
 // Now bound by the vector instructions of the walk.  Measured there, against
-// partials summed straight into the 2D gradients: 9.31 -> 4.33 ms; 500k
-// Gaussians at 1245x825 395 -> 298 us, 3M at 1920x1080 with a quarter of them
-// active 628 -> 556 us.  What sums and suffix would save and the gradients of
-// needles do not allow (row_sum9, alpha_gradient, the conic of g2d_component):
-// 3.69 ms, 225 us, 490 us.
+// partials summed straight into the 2D gradients: 9.31 -> 3.87 ms; 500k
+// Gaussians at 1245x825 395 -> 279 us, 3M at 1920x1080 with a quarter of them
+// active 628 -> 550 us; one list of 4,000 entries, where the walk's latency is
+// all, 434 -> 410 us.  What the gradients of needles do not allow (a scalar
+// suffix, a shorter tree, the conic applied to the sums: row_sum9,
+// alpha_gradient, g2d_component) made 3.69 ms, 225 us and 490 us of 4.33, 298
+// and 556, measured before the record indices were read once per round.
 template <bool MASKED, bool DET>
 __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__ rec, const int32_t* __restrict__ bin,
                                                        const uint32_t* __restrict__ vals,
@@ -1131,12 +1123,8 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   __shared__ RoundLds<kBatch, true> s_round;
   // the staged entries' sums over the workgroup; all zero at the start of a round
   __shared__ Acc s_acc[DET ? 1 : kBatch * kG2d];
-  __shared__ uint8_t s_stream[kWaves][kGroups][kBatch];
+  __shared__ alignas(4) uint8_t s_stream[kWaves][kGroups][kBatch];
   __shared__ uint32_t s_last[kWaves * kGroups];  // largest `last` of each group
-  for (int q = threadIdx.x; q < kWaves * kGroups * kBatch / 4; q += kBlock)
-    reinterpret_cast<AliasedU32*>(&s_stream[0][0][0])[q] = 0;
-  if (!DET)
-    for (int q = threadIdx.x; q < kBatch * kG2d; q += kBlock) s_acc[q] = Acc(0);
   const WorkItem wi = work_item(order, ranges, nsplit, vs.tiles_total, false);
   if (wi.skip) return;
   const int32_t tile = wi.tile;
@@ -1185,6 +1173,13 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
 #pragma unroll
   for (int k = 0; k < kWaves * kGroups; ++k) bjmax = s_last[k] > bjmax ? s_last[k] : bjmax;
   bjmax = uniform_u32(bjmax);
+  if (bjmax == 0u) return;
+  // the first offset of an empty stream is unused, but it is read: keep it in range
+  if (threadIdx.x < kWaves * kGroups) s_stream[threadIdx.x / kGroups][threadIdx.x % kGroups][0] = 0;
+  if (!DET) {
+    const int slots = bjmax < (uint32_t)kBatch ? (int)bjmax : kBatch;  // no round is longer
+    for (int q = threadIdx.x; q < slots * kG2d; q += kBlock) s_acc[q] = Acc(0);
+  }
   const int32_t ix0 = tx * kTile + (rp ? (wi.quarter & 1) * 8 : 0), iy0 = ty * kTile + (rp ? (wi.quarter >> 1) * 8 : 0);
   // Rounds cover [base, top) downwards from start + bjmax.  Staging pipeline:
   // the records of the next round and the list indices of the one after are
@@ -1340,20 +1335,30 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
       // Wave w adds the walked active entries of chunk w, which it tested, to
       // their records: seven entries of nine consecutive components at a time,
       // so an entry's adds leave in one or two requests.  It clears what it
-      // has read.
-      __syncthreads();
+      // has read.  The record indices are read again once for the chunk, while
+      // the wave waits for the others: a read per turn of the loop had its
+      // latency in every one (4.00 -> 3.87 ms there, 454 -> 410 us on the one
+      // list).
       const int fl = fresh(lane);
+      const bool mine = __builtin_amdgcn_inverse_ballot_w64(walked);  // (its index is valid)
+      const uint32_t who = mine ? vals[base + wv * kWave + fl] : 0u;
+      __syncthreads();
       const int fe = fl / kG2d, fc = fl - fe * kG2d;
       const int cnt = (int)__popcll(walked);
       uint8_t* list = &s_stream[wv][0][0];  // this wave's streams are walked
-      if (__builtin_amdgcn_inverse_ballot_w64(walked))
-        list[__builtin_amdgcn_mbcnt_hi((uint32_t)(walked >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)walked, 0u))] =
-            (uint8_t)(wv * kWave + fl);
+      AliasedU32* records = reinterpret_cast<AliasedU32*>(list + kWave);
+      static_assert(kWave * 5 <= kGroups * kBatch, "slot and record of a chunk's entries");
+      if (mine) {
+        const uint32_t at =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(walked >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)walked, 0u));
+        list[at] = (uint8_t)(wv * kWave + fl);
+        records[at] = who;
+      }
       wave_sync();
 #pragma unroll 1
       for (int e = fe < kWave / kG2d ? fe : kWave; e < cnt; e += kWave / kG2d) {
         const uint32_t k = list[e];
-        const uint32_t r = vals[base + k];  // a walked entry's index is valid
+        const uint32_t r = records[e];
         Acc* ap = s_acc + k * kG2d;
         const float val = g2d_component(fc, (float)ap[fc], fabsf(s_r2[k].w));
         ap[fc] = Acc(0);
