@@ -237,14 +237,21 @@ int32_t gs_bin_sort(const gs_projected_t* proj, const gs_camera_t* cams, int32_t
 
 /* a2-a4 in two halves around the pair count, which the caller needs to size
  * the lists.  gs_bin_tiles: what gs_bin_count returns, and the pairs counted
- * by tile: ranges [dev, u32 tiles_total][2] holds what gs_bin_lists needs of
- * them, tile_order [dev, u32 tiles_total] is final.  gs_bin_lists: vals, keys
- * (may be NULL), ranges and tile_order as gs_bin_sort gives them, from the
- * same proj, cameras, offsets, stats, ranges, tile_order and count workspace,
- * left as gs_bin_tiles left them.  With tile_order NULL, with the look-back sort selected
- * (gs_sort_set_algorithm) or with very long lists the radix sort of
- * gs_bin_sort makes the lists; the results are the same.  gs_sort_status reads
- * sort_ws.  gs_bin_tiles synchronises `stream`. */
+ * by tile where that pays: then stats->max_list > 0, ranges [dev, u32
+ * tiles_total][2] holds what gs_bin_lists needs of them and tile_order [dev,
+ * u32 tiles_total] is final.  With max_list 0 ranges and tile_order hold
+ * nothing of use yet (they may be unwritten) and gs_bin_lists writes both.
+ * gs_bin_lists: vals, keys (may be NULL), ranges and tile_order as gs_bin_sort
+ * gives them, from the same proj, cameras, offsets, stats, ranges, tile_order
+ * and count workspace, left as gs_bin_tiles left them.  It moves the ends in
+ * ranges, so it is called once per gs_bin_tiles (gs_bin_sort may be called with
+ * the same stats and offsets at any time).  With tile_order NULL, with the
+ * look-back sort selected (gs_sort_set_algorithm), a view of more than 32,768
+ * pixels width or 524,288 tiles in all, records far out of spatial order, few
+ * records that all cover the view, records whose bin.w is not what their boxes
+ * give, or lists of more than 65,536 entries the radix sort of gs_bin_sort makes
+ * the lists; the results are the same.  gs_sort_status reads sort_ws.
+ * gs_bin_tiles synchronises `stream`. */
 int32_t gs_bin_tiles(const gs_projected_t* proj, const gs_camera_t* cams, int32_t V, int64_t n, uint32_t* offsets,
                      gs_bin_stats_t* stats, uint32_t* ranges, uint32_t* tile_order, void* count_ws,
                      size_t count_ws_bytes, void* stream);
