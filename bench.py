@@ -43,7 +43,7 @@ PROJECT_BWD_BYTES_PER_ACTIVE = 59 * 4 + 59 * 4 + 36 + 16  # params read, grads w
 PROJECT_BWD_BYTES_PER_INACTIVE = 59 * 4 + 1     # zero rows written, mask read
 RENDER_FWD_BYTES_PER_PAIR = 4 + 8 + 48          # list index, pixel box, the 48 record bytes compositing reads
 RENDER_FWD_BYTES_PER_PIXEL = 12 + 4 + 4 + 4 + 4 + 4 + 1  # colour, depth, imax, T, last, count, hit
-RENDER_BWD_BYTES_PER_PAIR = 4 + 8 + 64 + 1      # list index, box, full record, active flag
+RENDER_BWD_BYTES_PER_PAIR = 4 + 8 + 48 + 1      # list index, box, the 48 record bytes read, active flag
 RENDER_BWD_BYTES_PER_PIXEL = 12 + 4 + 4         # dL/dC, T, last
 BIN_PARTS = {"count": ["k_tile_start", "k_tile_count", "k_tile_scan", "k_tile_offsets", "k_count_reduce",
                        "k_count_down"],

@@ -278,8 +278,9 @@ __global__ __launch_bounds__(kBlock) void k_project(ProjArgs pa, ViewSet vs) {
 // SH coefficients stay in registers from the first view that draws it: 256
 // VGPRs, two waves per SIMD, which the independent double instructions of a
 // record (its bound now) keep busy.  Reading the coefficients again for each
-// view at four waves instead spilled, 3626 us.  1M Gaussians, 16 views in two
-// calls: 1159 -> 784 us; 500k, 8 views: 179 -> 134 us.
+// view at four waves instead spilled (1M Gaussians in 16 views 3626 us).
+// Surfaces of 500k Gaussians in 8 views: 156 us by record, 122 so; 1.5M in 8
+// views 582 and 339.  Not with tile culling, see kViewsMinRows.
 template <int DEG>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void k_project_views(ProjArgs pa,
                                                                                                    ViewSet vs) {

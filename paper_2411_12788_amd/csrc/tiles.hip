@@ -13,9 +13,10 @@
 //   5. k_tile_sort     each run sorted in LDS, record indices written
 // The radix sort of (tile | depth) keys moves every pair through memory about
 // sixteen times (five to six passes of an up-sweep and a scatter) in nineteen
-// launches; here a pair is written once and read once.  Lists longer than
-// kTileMaxList, and scenes that are not in spatial order (k_tile_start), go to
-// the radix sort.
+// launches; here a pair is written once and read once (in lists of more than
+// kLongCap entries once per slice).  Lists longer than kTileMaxList, scenes that
+// are not in spatial order or whose boxes all cover the view (k_tile_start), and
+// records whose own counts are not what their boxes give go to the radix sort.
 #include "common.hpp"
 #include "tiles.hpp"
 
