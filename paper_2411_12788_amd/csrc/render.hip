@@ -376,6 +376,9 @@ __device__ __forceinline__ uint64_t test_round(RoundLds<BATCH, PER_CHUNK>& s, co
 // Entries of this wave's groups, `unit` per staged entry; n[g]: their counts.
 // By chunk, in a split work item: n[c] is where chunk c's part of the one
 // group's stream ends (FILL: filled up with kNoEntry to a multiple of four).
+// Without FILL (the backward, which reads no offset past a stream's end, but the
+// first one of an empty stream) every stream begins with an offset in range,
+// whatever the flush of the round before has left there.
 constexpr uint16_t kNoEntry = 0xffff;
 __device__ __forceinline__ int fill_four(uint16_t* stream, int n, int lane) {
   const int fill = -n & 3;
@@ -397,6 +400,10 @@ __device__ __forceinline__ void make_streams(const RoundLds<BATCH, PER_CHUNK>& s
           (T)((c * kWave + lane) * unit);
     return (int)__popcll(m);
   };
+  if constexpr (!FILL) {
+    if (lane < kGroups) stream[lane][0] = 0;
+    wave_sync();
+  }
   if (by_chunk) {
     int at = 0;
 #pragma unroll
@@ -1174,8 +1181,6 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   for (int k = 0; k < kWaves * kGroups; ++k) bjmax = s_last[k] > bjmax ? s_last[k] : bjmax;
   bjmax = uniform_u32(bjmax);
   if (bjmax == 0u) return;
-  // the first offset of an empty stream is unused, but it is read: keep it in range
-  if (threadIdx.x < kWaves * kGroups) s_stream[threadIdx.x / kGroups][threadIdx.x % kGroups][0] = 0;
   if (!DET) {
     const int slots = bjmax < (uint32_t)kBatch ? (int)bjmax : kBatch;  // no round is longer
     for (int q = threadIdx.x; q < slots * kG2d; q += kBlock) s_acc[q] = Acc(0);

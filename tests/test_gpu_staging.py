@@ -94,3 +94,54 @@ def test_slots_without_an_entry(gpu_lib, form, n):
                 for k in og:
                     got = _np(grads[k])[..., :sc.n]
                     assert np.isfinite(got).all() and H.rel_l2(got, og[k]) <= H.GRAD_REL_L2, (k, m is None, det)
+
+
+def test_flushed_rounds_leave_no_offsets(gpu_lib):
+    """Three rounds of 192 entries in one tile.  What the workgroup leaves in LDS
+    between two of them must not be taken for an offset: in the first round
+    walked (the list's last) entry 32 has a record index whose low byte, 216, is
+    no staging slot, and lands where the stream of group 1 of the first wave
+    begins; that group has no entry in the second round, in which the bytes that
+    a slot 216 would be read from are not a number; its one entry is in the
+    third."""
+    R = H.raster()
+    n, side, f = 1024, 16, 40.0
+    cam = identity_camera(side, side, f)
+    at = np.zeros((576, 2), dtype=int)
+    at[:] = (3, 2)                        # quarter and group of each list position
+    for k in (10, 20, 30, 127):
+        at[384 + k] = (0, 2)
+    for k in (1, 2, 130):
+        at[192 + k] = (0, 2)
+    at[50] = (0, 1)
+    index = np.arange(576)
+    index[384 + 32] = 2 * 256 + 216       # 728: beyond the others
+    q, grp = at[:, 0], at[:, 1]
+    u, v = 8 * (q & 1) + 4 * (grp & 1) + 2.0, 8 * (q >> 1) + 4 * (grp >> 1) + 2.0
+    z = 2.0 + 0.01 * np.arange(576)
+    g = gs_inputs.rng(9)
+    means, scales, opacity = np.tile((0.0, 0.0, 3.0), (n, 1)), np.full((n, 3), 0.01), np.zeros(n)
+    means[index] = np.stack([(u - side / 2) / f * z, (v - side / 2) / f * z, z], 1)
+    scales[index] = g.uniform(0.1, 0.3, size=(576, 3)) * z[:, None] / f
+    opacity[index] = np.where((at == (3, 2)).all(1), g.uniform(0.012, 0.016, size=576), 0.05)
+    opacity[index[50]] = 0.3
+    sh = gs_inputs.rng(10).normal(0.0, 0.2, size=(16, 3, n)).astype(np.float32)
+    sc = scene_from(means, scales, g.normal(size=(n, 4)), opacity, sh=sh, degree=3)
+    ds = R.DeviceScene.from_numpy(sc)
+    opts, o, Pn = R.RasterOpts(), oracle.Opts(), side * side
+    proj = R.project(ds, [cam], opts)
+    binned = R.bin(proj, [cam], n)
+    assert np.array_equal(_np(binned.vals), index)
+    frame = R.render_forward(ds, proj, binned, [cam], opts)
+    assert int(frame.last.max()) == 576  # the rounds begin at the list's end
+    p = oracle.Params.of(sc)
+    orc = oracle.forward_view(p, cam, o)
+    flips, _ = H.compare_forward(frame, orc, slice(0, Pn), "flushed rounds", p, cam, o)
+    dldc = gs_inputs.normal_image(3, Pn, 63, scale=1.0 / Pn)
+    og, _ = H.backward_views(p, [cam], o, [dldc.T.astype(np.float64)], flips=[flips])
+    for mask in (None, np.ones(n, dtype=np.uint8)):
+        grads, g2d = R.render_backward(ds, proj, binned, [cam], opts, frame, torch.from_numpy(dldc).cuda(),
+                                       None if mask is None else torch.from_numpy(mask).cuda())
+        assert torch.isfinite(g2d).all()
+        for k in og:
+            assert H.rel_l2(_np(grads[k])[..., :n], og[k]) <= H.GRAD_REL_L2, k
