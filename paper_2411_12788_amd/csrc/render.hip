@@ -1076,14 +1076,23 @@ __device__ __forceinline__ float g2d_component(int c, float x, float opacity) {
 // 36 lanes, more than the iteration's vector instructions take), ds_add_f64 for
 // 8 cycles in all.  So the accumulators are double where every Gaussian is
 // active, and float under an active mask, where few lanes add and the longer
-// rounds are worth more.
+// rounds are worth more.  The sums of a group that does not composite the entry
+// are zeros and are not added, unless dL/dcolour is not finite somewhere (0
+// times it is NaN): then (`strict`) only groups with a lane in cm are let through.
+// `on`: the lanes that may emit.
+__device__ __forceinline__ uint64_t rows_of(uint64_t lanes) {  // all lanes of the rows that have one
+  constexpr uint64_t kRow = 0x0001000100010001ull;
+  lanes |= (lanes >> 8) & 0x00ff00ff00ff00ffull;
+  lanes |= (lanes >> 4) & 0x000f000f000f000full;
+  lanes |= (lanes >> 2) & 0x0003000300030003ull;
+  lanes = (lanes | (lanes >> 1)) & kRow;
+  return (lanes << 16) - lanes;
+}
 template <bool DET, typename Acc>
 __device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ part, uint32_t* __restrict__ pmask,
-                                             uint32_t k, uint32_t base, int g16, int slot, uint64_t cm, int grp,
-                                             float val) {
-  if (slot < 0) return;
+                                             uint32_t k, uint32_t base, int g16, int slot, uint64_t on, float val) {
+  if (!__builtin_amdgcn_inverse_ballot_w64(on)) return;
   if (DET) {
-    if (((cm >> (16 * grp)) & 0xffffull) == 0) return;
     const uint32_t j = base + k;
     part[((int64_t)j * 16 + g16) * kG2d + slot] = val;
     if (slot == 8) atomicOr(pmask + j, 1u << g16);
@@ -1166,6 +1175,9 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
   float S[3] = {T * op.bg[0], T * op.bg[1], T * op.bg[2]};  // colour composited behind
   const int slot = sum_slot(lane);  // the sum this lane emits after row_sum9, or -1
   const ChannelPixels gm = channel_pixels(g[0], g[1], g[2], lane);
+  const uint64_t emitters = __builtin_amdgcn_ballot_w64(slot >= 0);
+  const bool strict = __builtin_amdgcn_ballot_w64(!(fabsf(g[0]) < INFINITY && fabsf(g[1]) < INFINITY &&
+                                                    fabsf(g[2]) < INFINITY)) != 0;
   {
     uint32_t m = lst;  // over the 16 lanes of a group; split rows hold the same pixels
 #pragma unroll
@@ -1288,8 +1300,10 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         S[2] += u2.total;
         // (a weight is positive wherever the entry is composited)
         const uint64_t cm = __builtin_amdgcn_ballot_w64(wa > 0.f);
-        if (cm != 0)
-          emit_partial<DET>(s_acc, part, pmask, off >> 4, base, g16, slot, cm, grp, row_sum9(pv, wa, gm, lane));
+        if (cm == 0) continue;
+        uint64_t on = emitters;
+        if (DET || strict) on &= rows_of(cm);
+        emit_partial<DET>(s_acc, part, pmask, off >> 4, base, g16, slot, on, row_sum9(pv, wa, gm, lane));
       }
       // One entry of the group's stream per iteration, latest first; the
       // transmittance is restored through them in reverse order.
@@ -1323,6 +1337,8 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         const float wa = !MASKED || act ? wgt : 0.f;
         const uint64_t cm = __builtin_amdgcn_ballot_w64(wa > 0.f);
         if (cm == 0) continue;
+        uint64_t on = emitters;
+        if (DET || strict) on &= rows_of(cm);
         float pv[6];
         // the clamped alpha has no gradient with respect to opacity or shape
         const float gal = (act && G2 < op.alpha_max) ? ga * al : 0.f;
@@ -1333,7 +1349,7 @@ __global__ __launch_bounds__(kBlock) void k_render_bwd(const float* __restrict__
         pv[2] = gx * dx;
         pv[3] = gx * dy;
         pv[4] = gy * dy;
-        emit_partial<DET>(s_acc, part, pmask, k, base, g16, slot, cm, grp, row_sum9(pv, wa, gm, lane));
+        emit_partial<DET>(s_acc, part, pmask, k, base, g16, slot, on, row_sum9(pv, wa, gm, lane));
       }
     }
     if (!DET) {
