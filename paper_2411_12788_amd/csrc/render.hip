@@ -1115,7 +1115,7 @@ __device__ __forceinline__ void emit_partial(Acc* s_acc, float* __restrict__ par
 // ~17 G requests/s), which bounded the kernel where most entries are active
 // (1M Gaussians, 16 views, 17.3M pixels, all active: 169M -> 31M requests).
 // Now bound by the vector instructions of the walk.  Measured there, against
-// partials summed straight into the 2D gradients: 9.31 -> 3.87 ms; 500k
+// partials summed straight into the 2D gradients: 9.31 -> 3.89 ms; 500k
 // Gaussians at 1245x825 395 -> 279 us, 3M at 1920x1080 with a quarter of them
 // active 628 -> 550 us; one list of 4,000 entries, where the walk's latency is
 // all, 434 -> 410 us.  What the gradients of needles do not allow (a scalar
